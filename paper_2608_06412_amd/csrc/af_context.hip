@@ -122,7 +122,7 @@ int fail(af_ctx *c, int code, const char *fmt, ...) {
                   __LINE__);                                                           \
   } while (0)
 
-int dev_alloc(af_ctx *c, void **p, int64_t bytes) {
+int dev_alloc_once(af_ctx *c, void **p, int64_t bytes) {
   if (bytes <= 0) bytes = 8;
   if (c->cfg.hbm_budget > 0 && c->bytes + bytes > c->cfg.hbm_budget)
     return fail(c, AF_ENOMEM, "HBM budget of %lld bytes exceeded (need %lld more)",
@@ -139,6 +139,28 @@ void dev_free(af_ctx *c, void *p, int64_t bytes) {
   hipFree(p);
   c->bytes -= bytes;
   c->allocs.erase(std::remove(c->allocs.begin(), c->allocs.end(), p), c->allocs.end());
+}
+
+// The tools' chunk tables only make scoring faster: an allocation that does
+// not fit otherwise takes their room.
+bool drop_chunks(af_ctx *c) {
+  bool any = false;
+  for (ToolDev &t : c->tools) {
+    if (!t.pent) continue;
+    dev_free(c, t.pent, chunk_bytes(t));
+    dev_free(c, t.pmeta, sizeof(uint4) * t.K);
+    t.pent = nullptr;
+    t.pmeta = nullptr;
+    any = true;
+  }
+  if (any) c->graph_stale = true;
+  return any;
+}
+
+int dev_alloc(af_ctx *c, void **p, int64_t bytes) {
+  int rc = dev_alloc_once(c, p, bytes);
+  if (rc != AF_OK && drop_chunks(c)) rc = dev_alloc_once(c, p, bytes);
+  return rc;
 }
 
 uint32_t pow2_at_least(int64_t n) {
@@ -536,10 +558,50 @@ static int tool_release(af_ctx *c, int32_t tool_id, hipStream_t s) {
     dev_free(c, t.nearp, sizeof(uint64_t) * c->cfg.max_points * 2 * mw);
     c->own_mask[tool_id] = 0;
   }
+  if (t.pent) {
+    dev_free(c, t.pent, chunk_bytes(t));
+    dev_free(c, t.pmeta, sizeof(uint4) * t.K);
+  }
   dev_free(c, t.c4begin, sizeof(uint32_t) * (t.K + 1));
   dev_free(c, t.c4flag, t.K);
   dev_free(c, t.c4entries, sizeof(uint32_t) * std::max<int64_t>(1, t.n_c4entries));
   memset(&t, 0, sizeof(t));
+  return AF_OK;
+}
+
+// The chunk form of the table (ToolDev::pent): the first chunk of every
+// orientation's body, then each orientation's other body chunks and its
+// corridor chunks; and the corridors' cells.
+static int tool_chunks(af_ctx *c, ToolDev &nt, const uint32_t *counts, hipStream_t s) {
+  const int32_t K = nt.K;
+  std::vector<uint32_t> n2(2 * (size_t)K), c4b(K + 1);
+  std::vector<uint8_t> flag(K);
+  HIP_TRY(c, hipMemcpy(n2.data(), counts, sizeof(uint32_t) * n2.size(), hipMemcpyDeviceToHost));
+  HIP_TRY(c, hipMemcpy(c4b.data(), nt.c4begin, sizeof(uint32_t) * c4b.size(), hipMemcpyDeviceToHost));
+  HIP_TRY(c, hipMemcpy(flag.data(), nt.c4flag, flag.size(), hipMemcpyDeviceToHost));
+  std::vector<uint4> meta(K);
+  int64_t at = K, cell = 0;
+  for (int32_t k = 0; k < K; ++k) {
+    const uint32_t nb = n2[2 * (size_t)k], nf = n2[2 * (size_t)k + 1];   // at most kTableMaxClass each
+    const uint32_t cells = nf > 0 && flag[k] ? c4b[k + 1] - c4b[k] : 0u;
+    meta[k] = make_uint4((uint32_t)at, nb | (nf << 16), (uint32_t)cell, cells);
+    at += (nb > 64 ? (nb - 1) / 64 : 0) + (nf + 63) / 64;
+    cell += cells;
+  }
+  nt.n_chunks = at + 4;
+  nt.n_pcells = cell;
+  if (chunk_bytes(nt) >= (int64_t(1) << 31)) return AF_OK;   // (offsets are 31 bits)
+  if (dev_alloc_once(c, (void **)&nt.pmeta, sizeof(uint4) * K) != AF_OK) return AF_OK;
+  if (dev_alloc_once(c, (void **)&nt.pent, chunk_bytes(nt)) != AF_OK) {
+    dev_free(c, nt.pmeta, sizeof(uint4) * K);
+    nt.pent = nullptr;
+    nt.pmeta = nullptr;
+    return AF_OK;   // scored without
+  }
+  HIP_TRY(c, hipMemcpyAsync(nt.pmeta, meta.data(), sizeof(uint4) * meta.size(),
+                            hipMemcpyHostToDevice, s));
+  HIP_TRY(c, hipStreamSynchronize(s));   // (meta is read by the copy)
+  if (launch_table_chunks(nt, s) != 0) return hip_check(c, "table chunks");
   return AF_OK;
 }
 
@@ -582,7 +644,7 @@ static int tool_finish(af_ctx *c, int32_t tool_id, ToolDev &nt, uint32_t *counts
     for (uint32_t e : he)
       reach = std::max({reach, std::abs(entry_x(e)), std::abs(entry_y(e)), std::abs(entry_z(e))});
     nt.reach = reach;
-    if (reach <= 255) {
+    if (reach <= kChunkReach) {
       std::vector<uint32_t> rel(total);
       for (uint32_t j = 0; j < total; ++j) {
         const uint32_t e = he[j];
@@ -595,6 +657,10 @@ static int tool_finish(af_ctx *c, int32_t tool_id, ToolDev &nt, uint32_t *counts
   }
   nt.n_entries = total;
   ALLOC(c, nt.xent, std::max<int64_t>(1, total));
+  if (nt.rent && K <= kNearK) {
+    const int rc = tool_chunks(c, nt, counts, s);
+    if (rc != AF_OK) return rc;
+  }
   nt.mask = c->mask;
   nt.nearp = c->nearp;
   ToolDev &t = c->tools[tool_id];

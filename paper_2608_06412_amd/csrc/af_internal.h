@@ -30,6 +30,9 @@ constexpr int kMaxSpan = 27;      // blocks touched by one return's cube (R <= 7
 constexpr int kMaxBand = 18;      // band samples per return (1.25 tau / (v/2) for R <= 7)
 constexpr int kMaxVp = 8;
 constexpr int kTableMaxClass = 16384;
+constexpr int kNearK = 1024;      // orientations the "near" and "chunk" scoring kernels take
+constexpr int kChunkReach = 255;  // largest offset component of the 4-byte entries that can be
+                                  // placed in any grid (ToolDev::rent, pent)
 constexpr uint32_t kUnknownWord = 0xAAAAAAAAu;  // 16 voxels coded "unknown, not cleared"
 
 // Status bits latched on the device.
@@ -201,9 +204,31 @@ struct ToolDev {
   // grid-independent 4-byte form, when every offset component is within
   // +-255: (ox + 256) | (oy + 256) << 10 | (oz + 256) << 20 | class << 30
   uint32_t *rent;       // [entries] or null
+  // the chunk scan's form, one buffer (null without rent, above kNearK
+  // orientations and where it does not fit): every orientation's body and
+  // corridor entries in chunks of 64 consecutive table entries, an entry as
+  // (ox + 256) | (oy + 256) << 12 | (oz + 256) << 22.  Chunk k (k < K) is
+  // the first chunk of orientation k's body; pmeta[k] = {index of its next
+  // chunk (the rest of its body, then its corridor), body entries | corridor
+  // entries << 16, its first corridor cell, cells}.  After the n_chunks
+  // 256-byte chunks follow the corridors' cells (see c4entries) as 12-byte
+  // records: (x + 256) | (y + 256) << 12 | (z + 256) << 22, and the corridor
+  // chunks the cell can hold entries of, as a 64-bit mask of groups of 2^s
+  // chunks (s the smallest with at most 64 groups).  No cells: an orientation
+  // without a list.
+  uint32_t *pent;
+  uint4 *pmeta;         // [K]
+  int64_t n_chunks;     // (four spare chunks included)
+  int64_t n_pcells;     // (128 spare cells follow)
   int64_t n_entries;
   int32_t reach;        // largest |offset| component over the table, voxels
 };
+
+// The parts of ToolDev::pent.
+__host__ __device__ inline int64_t chunk_cells_at(const ToolDev &t) { return 256 * t.n_chunks; }
+__host__ __device__ inline int64_t chunk_bytes(const ToolDev &t) {
+  return chunk_cells_at(t) + 12 * (t.n_pcells + 128);
+}
 
 // Table entry packing: 10-bit two's complement offsets, class in bits 30-31.
 __host__ __device__ inline uint32_t pack_entry(int ox, int oy, int oz, int cls) {
@@ -430,6 +455,8 @@ int launch_table_build(const ToolGeom &tg, int32_t K, const double *rot_dev,
                        uint32_t *entries_dev, int pass, hipStream_t s);
 
 int launch_table_grid(const ToolDev &t, const GridDev &g, hipStream_t s);
+// The chunk scan's chunks and cells (see ToolDev::pent) from the table.
+int launch_table_chunks(const ToolDev &t, hipStream_t s);
 int launch_table_coarse(int32_t K, const uint32_t *begin, const uint32_t *counts,
                         const uint32_t *entries, uint32_t *far_begin, uint32_t *ccounts,
                         uint32_t *cbegin, uint32_t *centries, uint8_t *cflag, int pass, int sh,

@@ -812,7 +812,6 @@ __device__ inline int nth_bit(uint64_t m, int r) {
 }
 
 constexpr int kLdsK = 256;    // orientations whose table heads the "swar" kernels stage in LDS
-constexpr int kNearK = 1024;  // orientations whose table offsets the "near" kernels stage in LDS
 constexpr int kLfK = 256;     // orientations whose first entries the "lds1" configurations stage
 
 // Hit test of one table entry at point s: arm samples (NEAR) hit on TSDF < r_c
@@ -1114,7 +1113,7 @@ __device__ inline bool corridor_clear4_sw(const ToolDev &t, const SwGrid &q, con
 // Entries [b, e) of orientation k after its first E: body entries finely,
 // then the corridor -- skipped when its 4^3 cells are clear (CO), finely
 // otherwise.  Canonical lookups stay the table-order count.
-template <int UN, int CO, int B1, int RE = 0, int LZ = 0, int UC = 0, int UB = 0>
+template <int UN, int CO, int B1, int RE = 0, int LZ = 0>
 __device__ inline bool scan_rest_sw(const Params &p, const ToolDev &t, const SwGrid &q,
                                     const SwFrame &f, int k, uint32_t b, uint32_t e, int body,
                                     uint32_t &lookups, uint32_t &cchecks, uint32_t &cclear,
@@ -1124,18 +1123,8 @@ __device__ inline bool scan_rest_sw(const Params &p, const ToolDev &t, const SwG
   if (!CO) return scan_fine_sw<UN, B1, RE, 0, LZ>(p, t, q, f, b, e, body, lookups, sbody, first);
   const uint32_t fb = t.far_begin[k];
   const uint32_t mid = fb > b ? fb : b;
-  if constexpr (UB > 0) {
-    // the body's first chunk alone (most blocked candidates end there), the
-    // rest UB chunks per step
-    const uint32_t c1 = b + 64u < mid ? b + 64u : mid;
-    if (!scan_fine_sw<UN, B1, RE, B1 ? 1 : 0, LZ>(p, t, q, f, b, c1, body, lookups, sbody, first))
-      return false;
-    if (!scan_fine_sw<UB, B1, RE, B1 ? 1 : 0, LZ>(p, t, q, f, c1, mid, body, lookups, sbody))
-      return false;
-  } else {
-    if (!scan_fine_sw<UN, B1, RE, B1 ? 1 : 0, LZ>(p, t, q, f, b, mid, body, lookups, sbody, first))
-      return false;
-  }
+  if (!scan_fine_sw<UN, B1, RE, B1 ? 1 : 0, LZ>(p, t, q, f, b, mid, body, lookups, sbody, first))
+    return false;
   if (mid >= e) return true;
   if (t.c4flag[k] != 0) {
     ++cchecks;
@@ -1145,11 +1134,7 @@ __device__ inline bool scan_rest_sw(const Params &p, const ToolDev &t, const SwG
       return true;
     }
   }
-  // the corridor: UC chunks per step (0: UN); a candidate that gets this far
-  // is mostly free and reads its whole corridor, so two chunks in flight
-  // hide one gather latency at little waste
-  return scan_fine_sw<UC ? UC : UN, B1, RE, B1 ? 2 : 0, LZ>(p, t, q, f, mid, e, body, lookups,
-                                                          sfar);
+  return scan_fine_sw<UN, B1, RE, B1 ? 2 : 0, LZ>(p, t, q, f, mid, e, body, lookups, sfar);
 }
 
 // Candidate-parallel scoring with grid-relative lookups (the configurations
@@ -1386,14 +1371,10 @@ __device__ inline void near_flush(ScoreCounterBlock &sc, NearAcc &a, int lane) {
 
 // One point of the "near" scoring (see k_score_near): label and first free
 // orientation of point i for tool t, whose begin offsets are s_begin.
-// LF: s_first holds, for every orientation k, its 64 entries after the arm
-// samples (lane l: entry min(begin[k] + 3 + l, begin[k + 1] - 1)), 4-byte
-// form, so a candidate's first step reads its entries from LDS.
-template <int UN, int CO, int B1, int PF, int RE, int LZ = 0, int UC = 0, int UB = 0, int LF = 0>
+template <int UN, int CO, int B1, int PF, int RE, int LZ = 0>
 __device__ inline void near_point(const Params &p, const PointsDev &pts, const ToolDev &t,
                                   const GridDev &g, const SwGrid &q, const uint32_t *s_begin,
-                                  int32_t mw, int64_t i, int lane, NearAcc &acc,
-                                  const uint32_t *s_first = nullptr) {
+                                  int32_t mw, int64_t i, int lane, NearAcc &acc) {
   constexpr uint32_t E = 3;   // the arm samples
   constexpr int F = 64 / PF;  // prefix entries per candidate when PF > 1
   static_assert(PF == 1 || PF == 2 || PF == 4 || PF == 8, "PF divides the wave");
@@ -1431,14 +1412,9 @@ __device__ inline void near_point(const Params &p, const PointsDev &pts, const T
       Ent pre{};
       auto first_step = [&](uint64_t o) {
         const int kn = 64 * w + (__ffsll((long long)o) - 1);
-        if constexpr (LF != 0) {
-          static_assert(RE == 1 && PF == 1 && UN == 1, "4-byte entries, one step");
-          return (Ent)s_first[kn * 64 + lane];
-        } else {
-          const uint32_t bn = s_begin[kn] + E, en = s_begin[kn + 1];
-          const uint32_t idx = bn + (uint32_t)lane;
-          return load_entry<RE>(t, idx < en ? idx : en - 1);
-        }
+        const uint32_t bn = s_begin[kn] + E, en = s_begin[kn + 1];
+        const uint32_t idx = bn + (uint32_t)lane;
+        return load_entry<RE>(t, idx < en ? idx : en - 1);
       };
       if (PF == 1 && open) pre = first_step(open);
       while (open && ff < 0) {
@@ -1501,7 +1477,7 @@ __device__ inline void near_point(const Params &p, const PointsDev &pts, const T
             body = __popcll(bm1);
             start = b + nin;
           }
-          if (scan_rest_sw<UN, CO, B1, RE, LZ, UC, UB>(
+          if (scan_rest_sw<UN, CO, B1, RE, LZ>(
                   p, t, q, f, kj, start, e, body, acc.lookups, acc.cchecks, acc.cclear, acc.sbody,
                   acc.sfar, c4, g.occ4, PF == 1 && UN == 1 ? &cur : nullptr)) {
             ff = (int16_t)kj;
@@ -1536,8 +1512,7 @@ __device__ inline void near_point(const Params &p, const PointsDev &pts, const T
 // only the undecided ones continue lane-parallel.  Requires K <= kNearK.
 // Same labels, first free orientations and canonical counts as the plain
 // scan.
-template <int NT, int UN, int FB, int CO, int B1, int DIAG, int PF = 1, int RE = 0, int UC = 0,
-          int UB = 0, int LF = 0>
+template <int NT, int UN, int FB, int CO, int B1, int DIAG, int PF = 1, int RE = 0>
 __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(8)))
 k_score_near(Params p, PointsDev pts, ToolDev t, GridDev g, int64_t n, int32_t mw,
              unsigned *work) {
@@ -1545,19 +1520,8 @@ k_score_near(Params p, PointsDev pts, ToolDev t, GridDev g, int64_t n, int32_t m
   if (n < 0) n = pts.sel ? (int64_t)*pts.n_sel : (int64_t)*pts.n_points;
   constexpr int NW = NT / 64;
   __shared__ uint32_t s_begin[kNearK + 1];
-  // LF: the first 64 entries after the arm samples of every orientation
-  // (K <= kLfK, 64 KiB), read from LDS instead of the table
-  __shared__ uint32_t s_first[LF ? kLfK * 64 : 1];
   const int K = t.K;
   for (int j = threadIdx.x; j <= K; j += NT) s_begin[j] = t.begin[j];
-  if constexpr (LF != 0) {
-    static_assert(NT == 1024, "two workgroups of 68 KiB LDS fill a CU's 160 KiB at 8 waves/SIMD");
-    for (int j = threadIdx.x; j < K * 64; j += NT) {
-      const uint32_t b = t.begin[j >> 6] + 3u, e = t.begin[(j >> 6) + 1];
-      const uint32_t idx = b + (uint32_t)(j & 63);
-      s_first[j] = load_entry<1>(t, idx < e ? idx : e - 1);
-    }
-  }
   __syncthreads();
   const SwGrid q = sw_grid(g);
   const int lane = lane_id();
@@ -1588,8 +1552,7 @@ k_score_near(Params p, PointsDev pts, ToolDev t, GridDev g, int64_t n, int32_t m
         !pts.sel ? i
         : FB > 0 ? (int64_t)__builtin_amdgcn_readlane(selv, (int)(FB - (batch_end - i)))
                  : (int64_t)__builtin_amdgcn_readfirstlane(pts.sel[i]);
-    near_point<UN, CO, B1, PF, RE, 1, UC, UB, LF>(p, pts, t, g, q, s_begin, mw, pi, lane, a,
-                                                  s_first);
+    near_point<UN, CO, B1, PF, RE, 1>(p, pts, t, g, q, s_begin, mw, pi, lane, a);
     if (a.lookups > (1u << 30)) near_flush<DIAG>(sc, a, lane);
     if (FB > 0) {
       if (++i >= batch_end) {
@@ -1604,6 +1567,444 @@ k_score_near(Params p, PointsDev pts, ToolDev t, GridDev g, int64_t n, int32_t m
     }
   }
   near_flush<DIAG>(sc, a, lane);
+}
+
+// ---------------------------------------------------------------------------
+// The chunk scan (the default configurations, "chunk").
+//
+// A candidate's body and corridor are tested 64 table entries at a time, one
+// per lane, against the one-bit plane, and the lookups are counted to the
+// deciding hit with a ballot.  The entry-per-lane scan before it walked
+// per-candidate begin offsets and mixed classes; its scalar control flow was
+// as long as its lookups.  What bounds this one is a chunk's chain of two
+// dependent reads (entries, then 64 gathered words: some 500 cycles; address
+// unit 69 %, vector ALU 62 % busy), so:
+//   - the corridor is not read whole: its 4^3 cells name the chunks that can
+//     hit (ToolDev::pent), and only those are read, two in flight;
+//   - the next candidate's chunk and range are requested before the current
+//     one is tested;
+//   - what depends on the point alone is computed for a batch of points, a
+//     lane each; loops have one exit and no lane-dependent branch, so that
+//     they stay plain scalar control flow.
+// Scoring, before and after (whole call): 1.55 M points x 256 orientations of
+// a tree survey 3340 -> 2500 us; 310 k x 291 790 -> 520 us (the kernel);
+// eight tools of 512 on 0.55 M points 15.9 -> 10.3 ms; four streams in one
+// launch 8.6 -> 5.1 ms.
+//
+// An entry's fields leave room for the carries of one add: bits 0-2 of the
+// sum are x in the brick and 3-9 the brick's x, 12-14 and 15-21 y, 22-24 and
+// 25-31 z.
+
+// What a wave accumulates (look: its uniform part; the others per lane).
+struct ChunkAcc {
+  uint32_t labv, tests, arm, lookv;   // labv as in NearAcc
+  uint32_t look;
+};
+
+// A grid and a tool as the chunk scan reads them.  (Few scalar registers: one
+// buffer per side, constants that only vector instructions use in vector
+// registers.)
+struct ChunkGrid {
+  const char *occ1, *occ4;
+  uint32_t nbricks;
+  uint32_t gx, gxy;
+  int32_t g0[3];
+};
+struct ChunkTool {
+  __amdgpu_buffer_rsrc_t tab;                              // ToolDev::pent
+  const __attribute__((address_space(4))) uint32_t *meta;  // wave-uniform reads
+  uint32_t cell_at;   // this lane's record in the cells
+  int32_t mw, n_c;
+};
+
+__device__ inline ChunkGrid chunk_grid(const GridDev &g) {
+  ChunkGrid q;
+  q.occ1 = (const char *)g.occ1;
+  q.occ4 = (const char *)g.occ4;
+  q.nbricks = (uint32_t)g.gd[0] * (uint32_t)g.gd[1] * (uint32_t)g.gd[2];
+  q.gx = (uint32_t)g.gd[0];
+  q.gxy = (uint32_t)g.gd[0] * (uint32_t)g.gd[1];
+  for (int a = 0; a < 3; ++a) q.g0[a] = g.g0[a];
+  return q;
+}
+
+__device__ inline ChunkTool chunk_tool(const Params &p, const ToolDev &t) {
+  ChunkTool c;
+  c.tab = __builtin_amdgcn_make_buffer_rsrc((void *)t.pent, (short)0, (int)(uint32_t)chunk_bytes(t),
+                                            0x00020000);
+  c.meta = (const __attribute__((address_space(4))) uint32_t *)(const uint32_t *)t.pmeta;
+  c.cell_at = (uint32_t)chunk_cells_at(t) + 12u * (uint32_t)lane_id();
+  c.mw = (t.K + 63) / 64;
+  c.n_c = p.n_c;
+  asm volatile("" : "+v"(c.cell_at), "+v"(c.n_c));
+  return c;
+}
+
+// The plane seen from one point.
+struct ChunkFrame {
+  __amdgpu_buffer_rsrc_t occ;   // the one-bit plane from the point's brick on (less the bias)
+  int32_t base;                 // that brick
+  uint32_t r;                   // the point's place in its brick, in the entry's fields
+};
+
+__device__ inline uint32_t mad24(uint32_t a, uint32_t b, uint32_t c) {
+  uint32_t d;
+  asm("v_mad_u32_u24 %0, %1, %2, %3" : "=v"(d) : "v"(a), "s"(b), "v"(c));
+  return d;
+}
+
+__device__ inline uint32_t chunk_word(const ChunkGrid &q, const ChunkFrame &f, uint32_t tt) {
+  const uint32_t brick = mad24(tt >> 25, q.gxy, mad24((tt >> 15) & 127u, q.gx, (tt >> 3) & 127u));
+  const uint32_t in = ((tt >> 19) & 0x38u) | ((tt >> 12) & 4u);   // 8 lz + 4 (ly >> 2)
+  return __builtin_amdgcn_raw_buffer_load_b32(f.occ, (int)((brick << 6) | in), 0, 0);
+}
+// The lanes below `rest` whose voxel's bit, lx + 8 (ly & 3), is set.
+__device__ inline uint64_t chunk_hits(uint32_t w, uint32_t tt, uint32_t rest) {
+  return __builtin_amdgcn_ballot_w64(__builtin_amdgcn_ubfe(w, (tt & 7u) | (__builtin_amdgcn_ubfe(tt, 12u, 2u) << 3), 1u) != 0u) &
+         __builtin_amdgcn_ballot_w64((uint32_t)lane_id() < rest);
+}
+
+// Counts the lookups up to and including the need-th hit of a chunk.
+__device__ inline void chunk_stop(ChunkAcc &a, uint64_t hits, uint32_t need) {
+  const uint32_t nth = __builtin_amdgcn_mbcnt_hi((uint32_t)(hits >> 32),
+                                                 __builtin_amdgcn_mbcnt_lo((uint32_t)hits, 1u));
+  const uint64_t at = hits & __builtin_amdgcn_ballot_w64(nth == need);
+  a.lookv += __builtin_amdgcn_inverse_ballot_w64(at) ? (uint32_t)lane_id() + 1u : 0u;
+}
+
+__device__ inline unsigned long long wave_total(uint32_t v) {
+  for (int off = 32; off >= 1; off >>= 1) v += (uint32_t)__shfl_xor((int)v, off);
+  return (unsigned long long)v;
+}
+
+__device__ inline void chunk_flush(ScoreCounterBlock &sc, ChunkAcc &a, int lane) {
+  if (lane < 4 && a.labv) {
+    unsigned long long *dst = lane == 0   ? &sc.n_confident
+                              : lane == 1 ? &sc.n_accessible
+                              : lane == 2 ? &sc.n_blocked
+                                          : &sc.n_no_candidate;
+    atomicAdd(dst, (unsigned long long)a.labv);
+  }
+  const unsigned long long tests = wave_total(a.tests), arm = wave_total(a.arm),
+                           look = wave_total(a.lookv) + a.look + arm;
+  if (lane == 0) {
+    if (tests) atomicAdd(&sc.canonical_tests, tests);
+    if (look) atomicAdd(&sc.canonical_lookups, look);
+    if (arm) atomicAdd(&sc.arm_lookups, arm);
+  }
+  a.labv = a.tests = a.arm = a.lookv = a.look = 0u;
+}
+
+template <int ctrl, int row_mask>
+__device__ inline uint32_t dpp_or(uint32_t x) {
+  return x | (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, ctrl, row_mask, 0xf, false);
+}
+// The OR of every lane's value.
+__device__ inline uint32_t wave_or(uint32_t x) {
+  x = dpp_or<0xb1, 0xf>(x);    // quad_perm [1, 0, 3, 2]
+  x = dpp_or<0x4e, 0xf>(x);    // quad_perm [2, 3, 0, 1]
+  x = dpp_or<0x141, 0xf>(x);   // row_half_mirror
+  x = dpp_or<0x140, 0xf>(x);   // row_mirror
+  x = dpp_or<0x142, 0xa>(x);   // row_bcast:15 into rows 1 and 3
+  x = dpp_or<0x143, 0xc>(x);   // row_bcast:31 into rows 2 and 3
+  return (uint32_t)__builtin_amdgcn_readlane((int)x, 63);
+}
+
+// The corridor's chunk groups that can hit: those named by a cell of its list
+// (n cells from `first`) that holds a voxel below r_c.  (A cell's bias is 128
+// bricks, 96 more than the entries'.)
+__device__ inline uint64_t chunk_groups(const ChunkTool &t, const ChunkGrid &q, const ChunkFrame &f,
+                                        uint32_t first, uint32_t n) {
+  const int32_t base = f.base - 96 * (int32_t)(1u + q.gx + q.gxy);
+  const __amdgpu_buffer_rsrc_t occ4 = __builtin_amdgcn_make_buffer_rsrc(
+      (void *)(q.occ4 + base), (short)0, (int)(q.nbricks - (uint32_t)base), 0x00020000);
+  const uint32_t lane = (uint32_t)lane_id();
+  const uint32_t r4 = (f.r >> 2) & 0x00401001u;   // the point's cell parities, in the cells' fields
+  uint32_t glo = 0u, ghi = 0u;
+  uint64_t any = 0ull;
+  auto gather = [&](uint32_t tt) {
+    const uint32_t brick =
+        mad24(tt >> 23, q.gxy, mad24((tt >> 13) & 511u, q.gx, (tt >> 1) & 511u));
+    return (uint32_t)__builtin_amdgcn_raw_buffer_load_b8(occ4, (int)brick, 0, 0);
+  };
+  auto test = [&](uint32_t byte, uint32_t tt, uint32_t lo, uint32_t hi, uint32_t rest) {
+    const uint32_t par = tt & 0x00401001u;   // the cell's parities, gathered into 3 bits
+    const uint32_t bit = (par | (par >> 11) | (par >> 20)) & 7u;
+    const bool hit = (((byte >> bit) & 1u) != 0u) & (lane < rest);
+    glo |= hit ? lo : 0u;
+    ghi |= hit ? hi : 0u;
+    any |= __builtin_amdgcn_ballot_w64(hit);
+  };
+  int at = (int)(12u * first);
+  uint32_t rest = n;
+  bool more;
+  do {   // two steps of 64 cells in flight
+    const auto c0 = __builtin_amdgcn_raw_buffer_load_b96(t.tab, (int)t.cell_at, at, 0);
+    const auto c1 = __builtin_amdgcn_raw_buffer_load_b96(t.tab, (int)t.cell_at, at + 768, 0);
+    const uint32_t t0 = (uint32_t)c0[0] + r4, t1 = (uint32_t)c1[0] + r4;
+    uint32_t o0 = gather(t0), o1 = gather(t1);
+    asm volatile("" : "+v"(o0), "+v"(o1));
+    test(o0, t0, (uint32_t)c0[1], (uint32_t)c0[2], rest);
+    test(o1, t1, (uint32_t)c1[1], (uint32_t)c1[2], rest > 64u ? rest - 64u : 0u);
+    more = rest > 128u;
+    rest -= 128u;
+    at += 1536;
+  } while (more);
+  if (!any) return 0ull;
+  return ((uint64_t)wave_or(ghi) << 32) | wave_or(glo);
+}
+
+// A point's candidate words: lanes [0, mw) the mask, [mw, 2 mw) and [2 mw,
+// 3 mw) the two arm-sample planes.
+__device__ inline uint64_t chunk_words(const ToolDev &t, int32_t mw, int64_t i, int lane) {
+  const uint64_t *m = t.mask + i * mw, *np = t.nearp + i * 2 * mw;
+  const int l = lane < 3 * mw ? lane : 0;
+  return *(l < mw ? m + l : np + (l - mw));
+}
+
+__device__ inline uint64_t bpermute64(uint64_t v, int lane) {
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_ds_bpermute(lane << 2, (int)(uint32_t)v);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_ds_bpermute(lane << 2, (int)(uint32_t)(v >> 32));
+  return ((uint64_t)hi << 32) | lo;
+}
+
+// One confident point: its label and first free orientation (-1: none).
+// r, base: its place in the brick, its brick less the entries' bias.  LF:
+// s_first holds the first chunk of every orientation (K <= kLfK).
+template <int LF>
+__device__ inline uint32_t chunk_point(const ChunkTool &t, const ChunkGrid &q, uint32_t r,
+                                       int32_t base, uint64_t words, int lane, ChunkAcc &acc,
+                                       const uint32_t *s_first, int32_t &ff) {
+  ChunkFrame f;
+  f.r = r;
+  f.base = base;
+  f.occ = __builtin_amdgcn_make_buffer_rsrc((void *)(q.occ1 + (int64_t)base * 64), (short)0,
+                                            (int)((q.nbricks - (uint32_t)base) << 6), 0x00020000);
+  asm volatile("" : "+v"(f.r));
+  const int lane4 = lane << 2;
+  auto chunk_at = [&](uint32_t c) {
+    return (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(t.tab, lane4, (int)(c << 8), 0);
+  };
+  auto first_chunk = [&](uint32_t k) {
+    if constexpr (LF != 0) return s_first[k * 64 + (uint32_t)lane];
+    else return chunk_at(k);
+  };
+  const uint64_t word = lane < t.mw ? words : 0ull;
+  const uint64_t p0 = bpermute64(words, lane + t.mw) & word,
+                 p1 = bpermute64(words, lane + 2 * t.mw) & word;
+  const uint64_t scan = word & ~(p0 | p1);   // not blocked by an arm sample
+  const uint32_t none =
+      __builtin_amdgcn_ballot_w64(word != 0ull) ? (uint32_t)AF_BLOCKED : (uint32_t)AF_NO_CANDIDATE;
+  uint64_t ow = __builtin_amdgcn_ballot_w64(scan != 0ull);   // the words to scan
+  ff = -1;
+  while ((ow != 0ull) & (ff < 0)) {
+    const int w = __builtin_ctzll(ow);
+    ow &= ow - 1;
+    uint64_t open = readlane64(scan, w);
+    // the first chunk and the chunk range of the next candidate are requested
+    // before the current candidate is scanned
+    uint32_t k = 64u * (uint32_t)w + (uint32_t)__builtin_ctzll(open);
+    uint32_t pre = first_chunk(k);
+    uint32_t m0 = t.meta[4 * k], m1 = t.meta[4 * k + 1];
+    do {
+      uint32_t tt = pre + f.r;
+      uint32_t wd = chunk_word(q, f, tt);
+      uint32_t chunk = m0;   // the chunk `nxt` holds
+      uint32_t nxt = chunk_at(chunk);
+      uint32_t rest = m1 & 0xffffu;   // body entries not yet tested
+      const uint32_t nf = m1 >> 16, kc = k;
+      open &= open - 1;
+      if (open) {
+        k = 64u * (uint32_t)w + (uint32_t)__builtin_ctzll(open);
+        pre = first_chunk(k);
+        m0 = t.meta[4 * k];
+        m1 = t.meta[4 * k + 1];
+      }
+      acc.look += rest;   // (less what a blocking chunk leaves untested)
+      uint32_t need = (uint32_t)__builtin_amdgcn_readfirstlane(t.n_c);
+      uint64_t h = chunk_hits(wd, tt, rest);
+      uint32_t n = (uint32_t)__popcll(h);
+      while ((n < need) & (rest > 64u)) {
+        need -= n;
+        rest -= 64u;
+        tt = nxt + f.r;
+        wd = chunk_word(q, f, tt);
+        nxt = chunk_at(++chunk);
+        h = chunk_hits(wd, tt, rest);
+        n = (uint32_t)__popcll(h);
+      }
+      bool blocked = n >= need;
+      if (!blocked) {
+        const uint32_t ncell = t.meta[4 * kc + 3];
+        uint64_t gr = nf ? ~0ull : 0ull;
+        if (ncell) gr = chunk_groups(t, q, f, t.meta[4 * kc + 2], ncell);
+        acc.look += nf;
+        if (gr) {
+          // the named chunks in order, two in flight (chunk: the corridor's first)
+          const uint32_t nch = (nf + 63u) / 64u, sh = nch <= 64u ? 0u : (nch <= 128u ? 1u : 2u);
+          uint32_t sub = 0;
+          auto take = [&]() {   // the next named chunk, nch when there is none
+            uint32_t c = (uint32_t)__builtin_ctzll(gr | (1ull << 63)) << sh | sub;
+            c = (gr != 0ull) & (c < nch) ? c : nch;
+            sub = (sub + 1u) & ((1u << sh) - 1u);
+            gr = sub ? gr : gr & (gr - 1ull);
+            return c;
+          };
+          uint32_t c0 = take(), c1 = take();
+          uint32_t e0 = chunk_at(chunk + c0), e1 = chunk_at(chunk + c1);
+          uint64_t h1;
+          uint32_t a0, a1;
+          bool more;
+          do {
+            const uint32_t t0 = e0 + f.r, t1 = e1 + f.r;
+            uint32_t w0 = chunk_word(q, f, t0), w1 = chunk_word(q, f, t1);
+            a0 = c0;
+            a1 = c1;
+            c0 = take();
+            c1 = take();
+            e0 = chunk_at(chunk + c0);
+            e1 = chunk_at(chunk + c1);
+            asm volatile("" : "+v"(w0), "+v"(w1));   // both gathers in flight together
+            h = chunk_hits(w0, t0, a0 < nch ? nf - 64u * a0 : 0u);
+            h1 = chunk_hits(w1, t1, a1 < nch ? nf - 64u * a1 : 0u);
+            more = ((h | h1) == 0ull) & (c0 < nch);
+          } while (more);
+          blocked = (h | h1) != 0ull;
+          a0 = h ? a0 : a1;
+          h = h ? h : h1;
+          rest = nf - 64u * a0;
+          need = 1u;
+        }
+      }
+      if (blocked) {
+        acc.look -= rest;
+        chunk_stop(acc, h, need);
+      } else {
+        ff = (int32_t)kc;
+      }
+    } while ((open != 0ull) & (ff < 0));
+  }
+  // visited: the candidates up to the free one, or all
+  const int fw = ff < 0 ? 64 : ff >> 6;
+  const uint64_t seen = lane < fw ? ~0ull : (lane == fw ? ~0ull >> (63 - (ff & 63)) : 0ull);
+  const uint64_t sw = word & seen, s0 = p0 & seen, s1 = p1 & seen;
+  acc.tests += (uint32_t)__popcll(sw);
+  acc.arm += (uint32_t)__popcll(s0) + 2u * (uint32_t)__popcll(s1) +
+             3u * (uint32_t)__popcll(sw & ~(s0 | s1));
+  return ff >= 0 ? (uint32_t)AF_ACCESSIBLE : none;
+}
+
+// Up to 64 work items, lane l holding item l's point (first + l stride).  The
+// records are read and placed in the grid for the whole batch at once, the
+// mask words one point ahead, so a point's scan does not start with a chain
+// of dependent reads; labels are written together.
+template <int LF>
+__device__ inline void chunk_batch(const PointsDev &pts, const ToolDev &t, const ChunkTool &ct,
+                                   const ChunkGrid &q, int64_t first, int64_t stride, int count,
+                                   int lane, ChunkAcc &acc, const uint32_t *s_first) {
+  const int64_t at = first + (lane < count ? lane : 0) * stride;
+  const int32_t pi = pts.sel ? pts.sel[at] : (int32_t)at;
+  const int32_t hn = pts.has_normal[pi];
+  int32_t s[3];
+  unpack_key(pts.key[pi], s[0], s[1], s[2]);
+  const uint32_t r = (uint32_t)(s[0] & 7) | ((uint32_t)(s[1] & 7) << 12) | ((uint32_t)(s[2] & 7) << 22);
+  constexpr int bias = 32;   // the entries' bias, in bricks
+  const int32_t base = ((s[0] >> 3) - q.g0[0] - bias) + (int32_t)q.gx * ((s[1] >> 3) - q.g0[1] - bias) +
+                       (int32_t)q.gxy * ((s[2] >> 3) - q.g0[2] - bias);
+  uint32_t out = 0xffff0000u;   // this lane's point: label | first free << 16
+  uint64_t next = chunk_words(t, ct.mw, __builtin_amdgcn_readlane(pi, 0), lane);
+  for (int b = 0; b < count; ++b) {
+    const uint64_t words = next;
+    next = chunk_words(t, ct.mw, __builtin_amdgcn_readlane(pi, b + 1 < count ? b + 1 : b), lane);
+    if (__builtin_amdgcn_readlane(hn, b) >= 0) {
+      int32_t ff;
+      const uint32_t label =
+          chunk_point<LF>(ct, q, (uint32_t)__builtin_amdgcn_readlane((int)r, b),
+                          __builtin_amdgcn_readlane(base, b), words, lane, acc, s_first, ff);
+      out = lane == b ? label | ((uint32_t)ff << 16) : out;
+    }
+  }
+  const uint32_t lab = out & 0xffu;
+  const uint64_t in = __builtin_amdgcn_ballot_w64(lane < count);
+  const uint32_t n0 = (uint32_t)__popcll(in & __builtin_amdgcn_ballot_w64(hn >= 0)),
+                 n1 = (uint32_t)__popcll(in & __builtin_amdgcn_ballot_w64(lab == AF_ACCESSIBLE)),
+                 n2 = (uint32_t)__popcll(in & __builtin_amdgcn_ballot_w64(lab == AF_BLOCKED)),
+                 n3 = (uint32_t)__popcll(in & __builtin_amdgcn_ballot_w64(lab == AF_NO_CANDIDATE));
+  acc.labv += lane == 0 ? n0 : lane == 1 ? n1 : lane == 2 ? n2 : lane == 3 ? n3 : 0u;
+  if (lane < count) {
+    t.label[pi] = (uint8_t)lab;
+    t.first_free[pi] = (int16_t)(out >> 16);
+  }
+}
+
+// The work items of a launch over its waves, in batches of kDealBatch: each
+// wave starts with a batch of its own and draws the others from one counter,
+// the next before the current one is scanned.  The counter takes some 13 ns a
+// draw, so a batch has 16 points (with 8, the 1.55 M points of a tree survey
+// take 194,000 draws and 2980 us instead of 2505).  A blocked point takes up
+// to a hundred times as long as a free one and blocked points lie together, so
+// a batch takes every kDealWindow-th item of a window of kDealBatch x
+// kDealWindow: 16 adjacent points kept single waves busy for the whole launch
+// (310 k points x 291 orientations: 520 us, 750 with adjacent points;
+// windows of 64 batches: 540; one window over all points: 515, but the eight tools'
+// masks no longer shared lines: 12.2 ms instead of 10.3).  Few items (at most
+// kDealFew a wave) go round by stride without the counter, whose atomics would
+// take longer than they even out.
+constexpr int kDealFew = 4, kDealBatch = 16, kDealWindow = 512;
+
+template <class F>
+__device__ inline void chunk_deal(int64_t n, int64_t waves, unsigned *work, int64_t wave, int lane,
+                                  F &&batch) {
+  const bool few = n <= kDealFew * waves;
+  constexpr int64_t window = (int64_t)kDealBatch * kDealWindow;
+  const int64_t stride = few ? waves : kDealWindow;
+  const int64_t batches = few ? waves : (n + window - 1) / window * kDealWindow;
+  int64_t b = wave;
+  while (b < batches) {
+    unsigned got = 0;
+    if ((lane == 0) & !few) got = atomicAdd(work, 1u);
+    const int64_t at = few ? b : b / kDealWindow * window + b % kDealWindow;
+    if (at < n) {
+      const int64_t left = (n - at + stride - 1) / stride;
+      batch(at, stride, (int)(left < kDealBatch ? left : kDealBatch));
+    }
+    b = few ? batches : waves + (int64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)got);
+  }
+}
+
+template <int NT, int LF>
+__global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(8)))
+k_score_chunk(Params p, PointsDev pts, ToolDev t, GridDev g, int64_t n, int32_t mw, unsigned *work) {
+  // n < 0: the point count on the device (recorded graphs, point lists)
+  if (n < 0) n = pts.sel ? (int64_t)*pts.n_sel : (int64_t)*pts.n_points;
+  constexpr int NW = NT / 64;
+  if ((int64_t)blockIdx.x * NW >= n) return;   // no wave of this workgroup gets an item
+  __shared__ uint32_t s_first[LF ? kLfK * 64 : 1];
+  if constexpr (LF != 0) {
+    for (int j = threadIdx.x; j < t.K * 64; j += NT) s_first[j] = t.pent[j];
+    __syncthreads();
+  }
+  const ChunkGrid q = chunk_grid(g);
+  const ChunkTool ct = chunk_tool(p, t);
+  const int lane = lane_id();
+  const int64_t wave =
+      (int64_t)blockIdx.x * NW + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  ScoreCounterBlock &sc = t.counters->s[(blockIdx.x * NW + (threadIdx.x >> 6)) % kStatSlots];
+  ChunkAcc a{};
+  chunk_deal(n, (int64_t)gridDim.x * NW, work, wave, lane,
+             [&](int64_t first, int64_t stride, int count) {
+               chunk_batch<LF>(pts, t, ct, q, first, stride, count, lane, a, s_first);
+               if (a.look > (1u << 30)) chunk_flush(sc, a, lane);
+             });
+  chunk_flush(sc, a, lane);
+}
+
+// Whether the chunk scan can place the entries in this grid with byte offsets
+// of 32 bits (from the base on, up to 65 brick layers; from the cells' base,
+// 128 layers of octant bytes): at 1 cm, every grid up to 60 m square.
+bool chunk_grid_ok(const GridDev &g) {
+  const int64_t layer = (int64_t)g.gd[0] * g.gd[1] + g.gd[0] + 1;
+  return 64 * (layer * 65 + (int64_t)g.gd[0] * g.gd[1] * g.gd[2]) < (int64_t(1) << 32);
 }
 
 // Several tools in one persistent launch: work item j is point j mod n of
@@ -1724,6 +2125,85 @@ k_score_near_jobs(const ScoreJob *jobs, int32_t n_jobs, unsigned *work) {
   if (cur >= 0) near_flush<0>(jp->t.counters->s[slot], a, lane);
 }
 
+// The chunk scan of several tools in one launch (see k_score_near_multi): a
+// batch of work items is split where it crosses from one tool to the next.
+template <int NT>
+__global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(8)))
+k_score_chunk_multi(Params p, PointsDev pts, const ToolDev *__restrict__ tools, ToolSet set, GridDev g,
+                    int64_t n, unsigned *work) {
+  if (n < 0) n = *pts.n_points;   // the point count on the device (recorded graphs)
+  const ChunkGrid q = chunk_grid(g);
+  const int lane = lane_id();
+  const int64_t wave =
+      (int64_t)blockIdx.x * (NT / 64) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int slot = (int)(wave % kStatSlots);
+  ChunkAcc a{};
+  int cur = -1;
+  chunk_deal(n * set.n, (int64_t)gridDim.x * (NT / 64), work, wave, lane,
+             [&](int64_t first, int64_t stride, int count) {
+               while (count > 0) {
+                 const int ti = __builtin_amdgcn_readfirstlane((int)(first / n));
+                 const ToolDev &t = tools[set.id[ti]];
+                 if (ti != cur) {
+                   if (cur >= 0) chunk_flush(tools[set.id[cur]].counters->s[slot], a, lane);
+                   cur = ti;
+                 }
+                 const ChunkTool ct = chunk_tool(p, t);
+                 const int64_t here = ((int64_t)(ti + 1) * n - first + stride - 1) / stride;
+                 const int c = __builtin_amdgcn_readfirstlane(here < count ? (int)here : count);
+                 chunk_batch<0>(pts, t, ct, q, first - (int64_t)ti * n, stride, c, lane, a, nullptr);
+                 if (a.look > (1u << 30)) chunk_flush(t.counters->s[slot], a, lane);
+                 first += c * stride;
+                 count -= c;
+               }
+             });
+  if (cur >= 0) chunk_flush(tools[set.id[cur]].counters->s[slot], a, lane);
+}
+
+// The chunk scan over several maps (see k_score_near_jobs).
+template <int NT>
+__global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(8)))
+k_score_chunk_jobs(const ScoreJob *__restrict__ jobs, int32_t n_jobs, unsigned *work) {
+  __shared__ int64_t s_start[kMaxJobs + 1];
+  if (threadIdx.x == 0) {
+    int64_t run = 0;
+    for (int j = 0; j < n_jobs; ++j) {
+      s_start[j] = run;
+      run += *jobs[j].pts.n_points;
+    }
+    s_start[n_jobs] = run;
+  }
+  __syncthreads();
+  const int lane = lane_id();
+  const int64_t wave =
+      (int64_t)blockIdx.x * (NT / 64) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int slot = (int)(wave % kStatSlots);
+  ChunkAcc a{};
+  int cur = -1;
+  chunk_deal(s_start[n_jobs], (int64_t)gridDim.x * (NT / 64), work, wave, lane,
+             [&](int64_t first, int64_t stride, int count) {
+               while (count > 0) {
+                 int ji = 0;   // the job whose range holds the item (empty jobs are passed over)
+                 while (s_start[ji + 1] <= first) ++ji;
+                 ji = __builtin_amdgcn_readfirstlane(ji);
+                 const ScoreJob &jb = jobs[ji];
+                 if (ji != cur) {
+                   if (cur >= 0) chunk_flush(jobs[cur].t.counters->s[slot], a, lane);
+                   cur = ji;
+                 }
+                 const ChunkTool ct = chunk_tool(jb.p, jb.t);
+                 const ChunkGrid q = chunk_grid(jb.g);
+                 const int64_t here = (s_start[ji + 1] - first + stride - 1) / stride;
+                 const int c = __builtin_amdgcn_readfirstlane(here < count ? (int)here : count);
+                 chunk_batch<0>(jb.pts, jb.t, ct, q, first - s_start[ji], stride, c, lane, a, nullptr);
+                 if (a.look > (1u << 30)) chunk_flush(jb.t.counters->s[slot], a, lane);
+                 first += c * stride;
+                 count -= c;
+               }
+             });
+  if (cur >= 0) chunk_flush(jobs[cur].t.counters->s[slot], a, lane);
+}
+
 using ScoreKernel = void (*)(Params, PointsDev, ToolDev, GridDev, int64_t, int32_t, unsigned *);
 
 struct ScoreVariant {
@@ -1733,6 +2213,7 @@ struct ScoreVariant {
   int max_k;         // largest K the configuration handles (0: any)
   int needs_rel;     // 1: only with the 4-byte entry form (offsets within +-255)
   const char *above_k;   // the configuration that runs above max_k (null: the plain one)
+  int chunk;         // 1: the chunk scan (needs ToolDev::pent and chunk_grid_ok, else kChunkElse)
 };
 
 // The tunable score configurations (identical results; speed only).
@@ -1749,13 +2230,10 @@ const ScoreVariant kVariants[] = {
     {k_score_near<256, 2, 8, 2, 1, 0, 1, 1>, 256, "near wg256 unroll2 dyn8 coarse4 bit rel", kNearK, 1},
     {k_score_near<512, 1, 8, 2, 1, 0, 1, 1>, 512, "near wg512 unroll1 dyn8 coarse4 bit rel", kNearK, 1},
     {k_score_near<256, 1, 8, 2, 1, 0, 2, 1>, 256, "near wg256 unroll1 dyn8 coarse4 bit prefix2 rel", kNearK, 1},
-    {k_score_near<256, 1, 8, 2, 1, 0, 1, 1, 2>, 256, "near wg256 unroll1 dyn8 coarse4 bit rel corr2", kNearK, 1},
-    {k_score_near<256, 1, 8, 2, 1, 1, 1, 1, 2>, 256, "near wg256 unroll1 dyn8 coarse4 bit rel corr2 diag", kNearK, 1},
-    {k_score_near<256, 1, 8, 2, 1, 0, 1, 1, 0, 2>, 256, "near wg256 unroll1 dyn8 coarse4 bit rel body2", kNearK, 1},
-    {k_score_near<1024, 1, 8, 2, 1, 0, 1, 1, 2, 0, 1>, 1024,
-     "near wg1024 unroll1 dyn8 coarse4 bit rel corr2 lds1", kLfK, 1,
-     "near wg256 unroll1 dyn8 coarse4 bit rel corr2"},
+    {k_score_chunk<256, 0>, 256, "chunk wg256", kNearK, 1, nullptr, 1},
+    {k_score_chunk<1024, 1>, 1024, "chunk wg1024 lds1", kLfK, 1, "chunk wg256", 1},
 };
+constexpr int kChunkElse = 6;   // where the chunk scan cannot run
 constexpr int kNumVariants = (int)(sizeof(kVariants) / sizeof(kVariants[0]));
 
 static int variant_index(const char *name) {
@@ -1765,6 +2243,21 @@ static int variant_index(const char *name) {
 }
 int g_resident[kNumVariants];   // workgroups per CU, from the occupancy query
 int g_num_cu = 0;
+
+int num_cu() {
+  if (g_num_cu == 0) {
+    int dev = 0, n = 0;
+    if (hipGetDevice(&dev) != hipSuccess) dev = 0;
+    if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n <= 0)
+      n = 256;
+    g_num_cu = n;
+  }
+  return g_num_cu;
+}
+
+// Workgroups of the chunk kernels a CU holds: their launch bounds give eight
+// waves per SIMD (the staged form's 64 KiB of LDS fits twice).
+constexpr int chunk_resident(int threads) { return 2048 / threads; }
 
 // Test hook: the PCA step alone, on caller-given moments [n][10] (cnt, sum
 // d [3], sum dd^T [6]).
@@ -1867,7 +2360,7 @@ int score_variants() { return kNumVariants; }
 
 // The configuration a new context uses (the fastest on the tree workload).
 int score_variant_default() {
-  return variant_index("near wg1024 unroll1 dyn8 coarse4 bit rel corr2 lds1");
+  return variant_index("chunk wg1024 lds1");
 }
 
 const char *score_variant_name(int v) {
@@ -1882,20 +2375,22 @@ void launch_score_multi(const Params &p, PointsDev pts, const ToolDev *tools_dev
                         const ToolDev *host_tools, const ToolSet &set, GridDev g, int64_t n,
                         unsigned *work, hipStream_t s, bool dev_n) {
   if (n <= 0 || set.n <= 0) return;
-  bool rel = true;
-  for (int i = 0; i < set.n; ++i) rel = rel && host_tools[i].rent != nullptr;
+  bool rel = true, chunk = chunk_grid_ok(g);
+  for (int i = 0; i < set.n; ++i) {
+    rel = rel && host_tools[i].rent != nullptr;
+    chunk = chunk && host_tools[i].pent != nullptr;
+  }
+  if (chunk) {
+    const int64_t wg = std::min<int64_t>((int64_t)chunk_resident(256) * num_cu(), (n * set.n + 3) / 4);
+    hipLaunchKernelGGL(k_zero, dim3(1), dim3(1), 0, s, work);
+    hipLaunchKernelGGL(k_score_chunk_multi<256>, dim3((unsigned)wg), dim3(256), 0, s, p, pts, tools_dev,
+                       set, g, dev_n ? (int64_t)-1 : n, work);
+    return;
+  }
   using MultiKernel = void (*)(Params, PointsDev, const ToolDev *, ToolSet, GridDev, int64_t,
                                unsigned *);
   const MultiKernel fn = rel ? k_score_near_multi<256, 1, 8, 2, 1, 1, 1>
                              : k_score_near_multi<256, 1, 8, 2, 1, 1, 0>;
-  if (g_num_cu == 0) {
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess) dev = 0;
-    if (hipDeviceGetAttribute(&g_num_cu, hipDeviceAttributeMultiprocessorCount, dev) !=
-            hipSuccess ||
-        g_num_cu <= 0)
-      g_num_cu = 256;
-  }
   int32_t words = 0;
   for (int i = 0; i < set.n; ++i) words += host_tools[i].K + 1;
   const size_t lds = sizeof(uint32_t) * (size_t)words;
@@ -1903,7 +2398,7 @@ void launch_score_multi(const Params &p, PointsDev pts, const ToolDev *tools_dev
   if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, 256, lds) != hipSuccess ||
       per_cu <= 0)
     per_cu = 1;
-  int64_t wg = (int64_t)per_cu * g_num_cu;
+  int64_t wg = (int64_t)per_cu * num_cu();
   const int64_t need = (n * set.n + 3) / 4;
   if (wg > need) wg = need;
   hipLaunchKernelGGL(k_zero, dim3(1), dim3(1), 0, s, work);
@@ -1915,10 +2410,11 @@ int launch_score_jobs(const ScoreJob *jobs_dev, const ScoreJob *jobs_host, int32
                       unsigned *work, hipStream_t s) {
   if (n_jobs <= 0) return 0;
   if (n_jobs > kMaxJobs) return -1;
-  bool rel = true;
+  bool rel = true, chunk = true;
   int64_t words = 0, np = 0;
   for (int j = 0; j < n_jobs; ++j) {
     rel = rel && jobs_host[j].t.rent != nullptr;
+    chunk = chunk && jobs_host[j].t.pent != nullptr && chunk_grid_ok(jobs_host[j].g);
     words += jobs_host[j].t.K + 1;
     if (jobs_host[j].t.K > kNearK) return -1;
     np += jobs_host[j].max_points;
@@ -1926,16 +2422,16 @@ int launch_score_jobs(const ScoreJob *jobs_dev, const ScoreJob *jobs_host, int32
   using JobKernel = void (*)(const ScoreJob *, int32_t, unsigned *);
   const JobKernel fn = rel ? k_score_near_jobs<256, 1, 8, 2, 1, 1, 1>
                            : k_score_near_jobs<256, 1, 8, 2, 1, 1, 0>;
-  if (g_num_cu == 0) {
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess) dev = 0;
-    if (hipDeviceGetAttribute(&g_num_cu, hipDeviceAttributeMultiprocessorCount, dev) !=
-            hipSuccess ||
-        g_num_cu <= 0)
-      g_num_cu = 256;
-  }
   const size_t lds = sizeof(uint32_t) * (size_t)words;
   if (lds > 64 * 1024) return -1;
+  if (chunk) {
+    const int64_t most = (int64_t)chunk_resident(256) * num_cu();
+    hipLaunchKernelGGL(k_zero, dim3(1), dim3(1), 0, s, work);
+    hipLaunchKernelGGL(k_score_chunk_jobs<256>,
+                       dim3((unsigned)std::max<int64_t>(1, std::min<int64_t>(most, (np + 3) / 4))),
+                       dim3(256), 0, s, jobs_dev, n_jobs, work);
+    return 0;
+  }
   // occupancy of the last (kernel, LDS size) asked for (a server asks every step)
   static const void *last_fn = nullptr;
   static size_t last_lds = 0;
@@ -1951,7 +2447,7 @@ int launch_score_jobs(const ScoreJob *jobs_dev, const ScoreJob *jobs_host, int32
     last_lds = lds;
     last_per_cu = per_cu;
   }
-  int64_t wg = (int64_t)per_cu * g_num_cu;
+  int64_t wg = (int64_t)per_cu * num_cu();
   const int64_t need = (np + 3) / 4;
   if (wg > need) wg = need;
   if (wg < 1) wg = 1;
@@ -1960,35 +2456,29 @@ int launch_score_jobs(const ScoreJob *jobs_dev, const ScoreJob *jobs_host, int32
   return 0;
 }
 
-static int effective_variant(int variant, const ToolDev &t) {
+static int effective_variant(int variant, const ToolDev &t, const GridDev *g = nullptr) {
   if (variant < 0 || variant >= kNumVariants) variant = 0;
   if (kVariants[variant].max_k && t.K > kVariants[variant].max_k)
     variant = kVariants[variant].above_k ? variant_index(kVariants[variant].above_k) : 0;
   if (kVariants[variant].max_k && t.K > kVariants[variant].max_k) variant = 0;
   if (kVariants[variant].needs_rel && !t.rent) variant = 0;
+  if (kVariants[variant].chunk && (!t.pent || (g && !chunk_grid_ok(*g)))) variant = kChunkElse;
   return variant;
 }
 
 bool score_variant_takes_list(int variant, const ToolDev &t) {
-  return strncmp(kVariants[effective_variant(variant, t)].name, "near", 4) == 0;
+  const ScoreVariant &v = kVariants[effective_variant(variant, t)];
+  return v.chunk || strncmp(v.name, "near", 4) == 0;
 }
 
 void launch_score(const Params &p, PointsDev pts, ToolDev t, GridDev g, int64_t n, int variant,
                   unsigned *work, hipStream_t s, bool dev_n) {
   int32_t mw = (t.K + 63) / 64;
   if (n <= 0) return;
-  variant = effective_variant(variant, t);
+  variant = effective_variant(variant, t, &g);
   if (pts.sel && !score_variant_takes_list(variant, t)) return;   // callers check first
   const ScoreVariant &v = kVariants[variant];
-  if (g_num_cu == 0) {
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess) dev = 0;
-    if (hipDeviceGetAttribute(&g_num_cu, hipDeviceAttributeMultiprocessorCount, dev) !=
-            hipSuccess ||
-        g_num_cu <= 0)
-      g_num_cu = 256;
-  }
-  if (g_resident[variant] == 0) {
+  if (!v.chunk && g_resident[variant] == 0) {
     int per_cu = 0;
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, v.fn, v.threads, 0) != hipSuccess ||
         per_cu <= 0)
@@ -1996,7 +2486,7 @@ void launch_score(const Params &p, PointsDev pts, ToolDev t, GridDev g, int64_t 
     g_resident[variant] = per_cu;
   }
   const int64_t nw = v.threads / 64;
-  int64_t wg = (int64_t)g_resident[variant] * g_num_cu;
+  int64_t wg = (int64_t)(v.chunk ? chunk_resident(v.threads) : g_resident[variant]) * num_cu();
   int64_t need = (n + nw - 1) / nw;
   if (wg > need) wg = need;
   hipLaunchKernelGGL(k_zero, dim3(1), dim3(1), 0, s, work);

@@ -255,7 +255,76 @@ __global__ void k_table_grid(const uint32_t *entries, int64_t n, int32_t gx, int
   }
 }
 
+// The chunk scan's chunks (see ToolDev::pent): one workgroup per orientation,
+// a wave per chunk.  Lanes past the class end hold the zero offset, which the
+// scan masks out.
+constexpr uint32_t kBias = 256u;
+constexpr uint32_t kZeroOffset = kBias | (kBias << 12) | (kBias << 22);
+
+__global__ void __launch_bounds__(256) k_table_chunks(ToolDev t) {
+  const int k = blockIdx.x, lane = threadIdx.x & 63;
+  const uint4 m = t.pmeta[k];
+  const uint32_t nb = m.y & 0xffffu, nf = m.y >> 16;
+  const uint32_t body = t.begin[k] + 3, far_ = body + nb;
+  const uint32_t cb = nb > 64 ? (nb + 63) / 64 : 1, cf = (nf + 63) / 64;
+  for (uint32_t j = threadIdx.x >> 6; j < cb + cf; j += 4) {
+    const uint32_t chunk = j == 0 ? (uint32_t)k : m.x + (j - 1);
+    const uint32_t lo = j < cb ? body + 64 * j : far_ + 64 * (j - cb);
+    const uint32_t end = j < cb ? body + nb : far_ + nf;
+    uint32_t v = kZeroOffset;
+    if (lo + lane < end) {
+      const uint32_t e = t.entries[lo + lane];
+      v = (uint32_t)(entry_x(e) + (int)kBias) | ((uint32_t)(entry_y(e) + (int)kBias) << 12) |
+          ((uint32_t)(entry_z(e) + (int)kBias) << 22);
+    }
+    t.pent[64 * (uint64_t)chunk + lane] = v;
+  }
+  // the spare chunks after the last one (read ahead, never tested)
+  if (k == 0) t.pent[64 * (t.n_chunks - 4) + threadIdx.x] = kZeroOffset;
+}
+
+// The corridors' cells (see ToolDev::pent), a workgroup per orientation: a
+// thread per cell collects the chunks whose entries can fall into it (per
+// axis, entry o falls into cells o >> 2 and (o + 3) >> 2 over the point's
+// positions in its own cell).
+__global__ void __launch_bounds__(256) k_table_cells(ToolDev t) {
+  const int k = blockIdx.x;
+  const uint4 m = t.pmeta[k];
+  const uint32_t nf = m.y >> 16, far_ = t.begin[k] + 3 + (m.y & 0xffffu);
+  const uint32_t chunks = (nf + 63) / 64;
+  const int sh = chunks <= 64 ? 0 : (chunks <= 128 ? 1 : 2);
+  uint32_t *cells = t.pent + chunk_cells_at(t) / 4;
+  for (uint32_t i = threadIdx.x; i < m.w; i += 256) {
+    const uint32_t c = t.c4entries[t.c4begin[k] + i];
+    const int cx = entry_x(c), cy = entry_y(c), cz = entry_z(c);
+    uint64_t groups = 0ull;
+    for (uint32_t j = 0; j < nf; ++j) {
+      const uint32_t e = t.entries[far_ + j];
+      const int x = entry_x(e), y = entry_y(e), z = entry_z(e);
+      const bool in = ((x >> 2) == cx || ((x + 3) >> 2) == cx) &&
+                      ((y >> 2) == cy || ((y + 3) >> 2) == cy) &&
+                      ((z >> 2) == cz || ((z + 3) >> 2) == cz);
+      if (in) groups |= 1ull << ((j >> 6) >> sh);
+    }
+    uint32_t *rec = cells + 3 * (uint64_t)(m.z + i);
+    rec[0] = (uint32_t)(cx + 256) | ((uint32_t)(cy + 256) << 12) | ((uint32_t)(cz + 256) << 22);
+    rec[1] = (uint32_t)groups;
+    rec[2] = (uint32_t)(groups >> 32);
+  }
+  if (k == 0 && threadIdx.x < 128) {   // spare cells after the last list (read, masked out)
+    uint32_t *rec = cells + 3 * (uint64_t)(t.n_pcells + threadIdx.x);
+    rec[0] = 256u | (256u << 12) | (256u << 22);
+    rec[1] = rec[2] = 0u;
+  }
+}
+
 }  // namespace
+
+int launch_table_chunks(const ToolDev &t, hipStream_t s) {
+  hipLaunchKernelGGL(k_table_chunks, dim3((unsigned)t.K), dim3(256), 0, s, t);
+  hipLaunchKernelGGL(k_table_cells, dim3((unsigned)t.K), dim3(256), 0, s, t);
+  return hipGetLastError() == hipSuccess ? 0 : -1;
+}
 
 int launch_table_grid(const ToolDev &t, const GridDev &g, hipStream_t s) {
   const int64_t n = t.n_entries;
