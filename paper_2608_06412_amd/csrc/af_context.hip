@@ -188,9 +188,8 @@ int alloc_scratch(af_ctx *c, int64_t cap) {
     dev_free(c, f.new_sorted, sizeof(int64_t) * ((f.cap + 255) / 256 * 256));
     dev_free(c, f.new_kslot, sizeof(int32_t) * f.cap);
     dev_free(c, f.touched, sizeof(int32_t) * f.cap * (kMaxSpan + kMaxBand));
-    dev_free(c, f.bin_cnt, sizeof(int32_t) * f.cap * (kMaxSpan + kMaxBand));
-    dev_free(c, f.bin_off, sizeof(int32_t) * (f.cap * (kMaxSpan + kMaxBand) + 1));
-    dev_free(c, f.bin_fill, sizeof(int32_t) * f.cap * (kMaxSpan + kMaxBand));
+    dev_free(c, f.rank, sizeof(int32_t) * f.cap * kMaxSpan);
+    dev_free(c, f.bin, sizeof(int2) * f.cap * (kMaxSpan + kMaxBand));
     dev_free(c, f.bin_list, sizeof(int32_t) * f.cap * kMaxSpan);
     memset(&f, 0, sizeof(f));
   }
@@ -203,9 +202,8 @@ int alloc_scratch(af_ctx *c, int64_t cap) {
   ALLOC(c, f.new_sorted, (cap + 255) / 256 * 256);
   ALLOC(c, f.new_kslot, cap);
   ALLOC(c, f.touched, cap * (kMaxSpan + kMaxBand));
-  ALLOC(c, f.bin_cnt, cap * (kMaxSpan + kMaxBand));
-  ALLOC(c, f.bin_off, cap * (kMaxSpan + kMaxBand) + 1);
-  ALLOC(c, f.bin_fill, cap * (kMaxSpan + kMaxBand));
+  ALLOC(c, f.rank, cap * kMaxSpan);
+  ALLOC(c, f.bin, cap * (kMaxSpan + kMaxBand));
   ALLOC(c, f.bin_list, cap * kMaxSpan);
   f.cap = cap;
   return AF_OK;
@@ -991,11 +989,9 @@ int af_integrate_frame(af_ctx *c, const float *xyz, int64_t n, const float origi
     launch_window_evict(c->map, c->pts, c->n_blocks, c->n_points, wlo, whi, s);
     c->win_shifts += 1;
   }
-  launch_set_frame_args(c->fargs, n, Q, frame, wlo, whi, s);
-  launch_frame_prep(xyz, c->fargs, n, c->p, c->map, c->pts, c->fs, c->counters, s);
+  launch_frame_prep(xyz, c->fargs, {n, Q, frame, wlo, whi}, n, c->p, c->map, c->pts, c->fs, c->counters, s);
   if (thaw) launch_window_thaw(c->map, c->pts, c->fs, c->counters, c->n_points, wlo, whi, s);
   launch_assign_blocks(c->map, c->fs, c->counters, c->fargs, s);
-  launch_commit_blocks(c->map, c->counters, s);
   if (thaw) launch_window_link(c->map, c->pts, c->n_points, wlo, whi, s);
   HIP_TRY(c, hipMemcpyAsync(c->counters_host, c->counters, offsetof(FrameCounters, fold),
                             hipMemcpyDeviceToHost, s));
@@ -1013,14 +1009,12 @@ int af_integrate_frame(af_ctx *c, const float *xyz, int64_t n, const float origi
   if ((rc = ensure_grid(c, s, rebuilt, shift)) != AF_OK) return rc;
   launch_touch_band(c->fargs, n, c->p, c->map, c->fs, c->counters, s);
   launch_points_append(h.n_new_points, c->map, c->pts, c->fs, c->counters, c->fargs, s);
-  launch_commit_points(c->pts, c->counters, s);
-  launch_points_view(c->fargs, n, c->p, c->pts, c->fs, s);
   // new blocks take evicted ids first
   int64_t nb_after = std::min<int64_t>(
       (int64_t)h.blocks_before + std::max<int64_t>(0, (int64_t)h.n_new_blocks - h.free_before),
       c->cfg.max_blocks);
   hipEvent_t t1 = timing_mark(c, s);
-  launch_integrate(c->fargs, n, c->p, c->map, c->fs, c->counters, c->grid,
+  launch_integrate(c->fargs, n, c->p, c->map, c->pts, c->fs, c->counters, c->grid,
                    std::max<int64_t>(1, std::min<int64_t>(nb_after, n * (kMaxSpan + kMaxBand))), s);
   hipEvent_t t2 = timing_mark(c, s);
   if (rebuilt) launch_grid_rebuild(c->p, c->map, c->grid, nb_after, s);
@@ -1391,14 +1385,13 @@ static int graph_record(af_ctx *c, hipStream_t s) {
   const int64_t cap = c->slot_cap, NP = c->cfg.max_points;
   const int32_t n_tools = c->g_n;
   HIP_TRY(c, hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal));
-  launch_frame_prep(c->slot_xyz, c->fargs, cap, c->p, c->map, c->pts, c->fs, c->counters, cs);
+  FrameArgs given{};   // set before each replay
+  given.n = -1;
+  launch_frame_prep(c->slot_xyz, c->fargs, given, cap, c->p, c->map, c->pts, c->fs, c->counters, cs);
   launch_assign_blocks(c->map, c->fs, c->counters, c->fargs, cs);
-  launch_commit_blocks(c->map, c->counters, cs);
   launch_touch_band(c->fargs, cap, c->p, c->map, c->fs, c->counters, cs);
   launch_points_append(cap, c->map, c->pts, c->fs, c->counters, c->fargs, cs);
-  launch_commit_points(c->pts, c->counters, cs);
-  launch_points_view(c->fargs, cap, c->p, c->pts, c->fs, cs);
-  launch_integrate(c->fargs, cap, c->p, c->map, c->fs, c->counters, c->grid,
+  launch_integrate(c->fargs, cap, c->p, c->map, c->pts, c->fs, c->counters, c->grid,
                    std::min<int64_t>(c->cfg.max_blocks, cap * (kMaxSpan + kMaxBand)), cs);
   launch_stick_status(c->counters, c->map.n_blocks, c->pts.n_points, cs);
   for (int32_t i = 0; i < n_tools; ++i)

@@ -69,6 +69,7 @@ struct FrameCounters {
   unsigned long long n_valid, n_dropped, pairs_applied, pairs_excluded;
   unsigned long long band_marks, voxels_folded;
   int32_t n_new_blocks, n_touched, n_new_points, status;
+  int32_t n_binned;    // (return, block) pairs given room in the bins
   int32_t n_changed;   // voxels that received a contribution (listed when fs.changed is set)
   int32_t bmin[3], bmax[3];
   int32_t blocks_before, points_before;
@@ -112,7 +113,8 @@ struct MapDev {
   uint32_t *clr;                 // [max_blocks * 16]
   uint32_t *surf;                // [max_blocks * 16]
   int32_t *touched;              // [max_blocks] last frame that touched the block
-  int32_t *tpos;                 // [max_blocks] position in that frame's touched list
+  int32_t *tpos;                 // [max_blocks] within a frame: the block's returns, then the
+                                 // start of its bin; 0 between frames
   int32_t *n_blocks;             // device counter (ids ever handed out)
   int64_t max_blocks;
   // sliding window only (null otherwise): ids of evicted blocks, reused
@@ -145,17 +147,17 @@ struct PointsDev {
 // Per-frame scratch, sized for `cap` returns.
 struct FrameScratch {
   int4 *P;            // fixed-point return + isqrt |P-Q| (0 when dropped)
-  int32_t *span;      // [cap * kMaxSpan] block hash slots of the cube span
-  int32_t *band;      // [cap * kMaxBand * 2] (hash slot, voxel index) pairs
+  // entry i of return r at [i * cap + r]
+  int32_t *span;      // [kMaxSpan * cap] blocks of the cube span: hash slots, then ids (-1: none)
+  int32_t *rank;      // [kMaxSpan * cap] the return's rank in that block's bin
+  int32_t *band;      // [2 kMaxBand * cap] hash slot (-2: no sample), voxel index
   int32_t *pslot;     // [cap] point hash slot
   int32_t *new_blocks;// [cap * (kMaxSpan + kMaxBand)] hash slots of new blocks
   int64_t *new_keys;  // [cap] new point keys
   int64_t *new_sorted;  // [cap rounded up to 256] the new keys, sorted within each 256-key tile
   int32_t *new_kslot; // [cap] their hash slots
   int32_t *touched;   // [cap * (kMaxSpan + kMaxBand)] touched block ids
-  int32_t *bin_cnt;   // [cap * (kMaxSpan + kMaxBand)] returns per touched block
-  int32_t *bin_off;   // [cap * (kMaxSpan + kMaxBand) + 1] their prefix
-  int32_t *bin_fill;  // [cap * (kMaxSpan + kMaxBand)] insertion cursors
+  int2 *bin;          // [cap * (kMaxSpan + kMaxBand)] their bins: start, returns
   int32_t *bin_list;  // [cap * kMaxSpan] return ids grouped by block
   int64_t cap;
   int32_t *changed;   // null, or [max_blocks * 512]: voxel addresses (block * 512 + index)
@@ -410,23 +412,21 @@ void launch_smooth_refine(const SmoothField &f, double v, const float *p, int64_
 void launch_stick_status(FrameCounters *c, const int32_t *n_blocks, const int32_t *n_points,
                          hipStream_t s);
 void launch_zero_words(void *p, int64_t bytes, hipStream_t s);   // a fill kernel (graph-safe)
-// nb: an upper bound of the frame's returns (sizes the launches)
-void launch_frame_prep(const float *xyz, const FrameArgs *fa, int64_t nb, const Params &p,
-                       MapDev m, PointsDev pts, FrameScratch fs, FrameCounters *c,
+// nb: an upper bound of the frame's returns (sizes the launches); fa_new: the
+// frame's arguments, set on the way (n < 0: fa holds them already)
+void launch_frame_prep(const float *xyz, FrameArgs *fa, const FrameArgs &fa_new, int64_t nb,
+                       const Params &p, MapDev m, PointsDev pts, FrameScratch fs, FrameCounters *c,
                        hipStream_t s);
 void launch_assign_blocks(MapDev m, FrameScratch fs, FrameCounters *c, const FrameArgs *fa,
                           hipStream_t s);
-void launch_commit_blocks(MapDev m, FrameCounters *c, hipStream_t s);
-void launch_integrate(const FrameArgs *fa, int64_t nb, const Params &p, MapDev m,
+// Viewpoints, bins, fold and bricks; the frame's new ids become part of the map.
+void launch_integrate(const FrameArgs *fa, int64_t nb, const Params &p, MapDev m, PointsDev pts,
                       FrameScratch fs, FrameCounters *c, GridDev g, int64_t max_touched,
                       hipStream_t s);
 void launch_touch_band(const FrameArgs *fa, int64_t nb, const Params &p, MapDev m,
                        FrameScratch fs, FrameCounters *c, hipStream_t s);
 void launch_points_append(int64_t n_new, MapDev m, PointsDev pts, FrameScratch fs,
                           FrameCounters *c, const FrameArgs *fa, hipStream_t s);
-void launch_commit_points(PointsDev pts, FrameCounters *c, hipStream_t s);
-void launch_points_view(const FrameArgs *fa, int64_t nb, const Params &p, PointsDev pts,
-                        FrameScratch fs, hipStream_t s);
 // Sliding window (Section 3.3).  On a shift, before the frame: blocks
 // outside the new box [lo, hi] are cleared and their ids freed, the block
 // hash is rebuilt from the live blocks, and points outside the box lose their
