@@ -61,8 +61,7 @@ struct af_ctx {
   bool have_q;
   // smoothed score: apron bricks and their tables (SmoothBuffers), grown on demand
   SmoothBuffers sm;
-  int64_t sm_T_cap;             // voxels of sm.T
-  int64_t sm_bid_cap;           // bricks of sm.bid and sm.bid9
+  int64_t sm_bid_cap;           // bricks of sm.bid9
   // cached normal axes of the eager scoring calls (allocated on first use)
   NormalCache ncache;
   int64_t nc_seen;              // points whose neighbourhood the cache reflects
@@ -1579,42 +1578,30 @@ static int smooth_prepare(af_ctx *c, hipStream_t s, SmoothField &f) {
   if (c->graph_dirty && (rc = graph_settle(c)) != AF_OK) return rc;
   if ((rc = regrid(c, s)) != AF_OK) return rc;
   SmoothBuffers &b = c->sm;
-  const int64_t nv = std::max<int64_t>(1, c->n_blocks * kBlockVox);
   const int64_t nb = std::max<int64_t>(1, c->grid_bricks);
   // every mapped block marks itself and its -1 neighbours: at most 8 aprons each
   const int64_t na = std::max<int64_t>(1, std::min<int64_t>(8 * c->n_blocks, c->grid_bricks));
-  if (nv > c->sm_T_cap || nb > c->sm_bid_cap || na > b.apron_cap || !b.count || !b.work) {
+  if (nb > c->sm_bid_cap || na > b.apron_cap || !b.count) {
     HIP_TRY(c, hipStreamSynchronize(s));
-    if (nv > c->sm_T_cap) {
-      if (b.T) dev_free(c, b.T, sizeof(float) * c->sm_T_cap);
-      b.T = nullptr;
-      c->sm_T_cap = 0;
-      const int64_t cap = std::min<int64_t>(c->cfg.max_blocks * kBlockVox, nv + nv / 2 + kBlockVox);
-      ALLOC(c, b.T, cap);
-      c->sm_T_cap = cap;
-    }
     if (nb > c->sm_bid_cap) {
-      if (b.bid) dev_free(c, b.bid, sizeof(int32_t) * c->sm_bid_cap);
       if (b.bid9) dev_free(c, b.bid9, sizeof(int32_t) * c->sm_bid_cap);
-      b.bid = b.bid9 = nullptr;
+      b.bid9 = nullptr;
       c->sm_bid_cap = 0;
-      ALLOC(c, b.bid, nb);
       ALLOC(c, b.bid9, nb);
       c->sm_bid_cap = nb;
     }
     if (na > b.apron_cap) {
-      if (b.T9) dev_free(c, b.T9, sizeof(float) * 729 * b.apron_cap);
+      if (b.T9) dev_free(c, b.T9, sizeof(float) * 729 * (b.apron_cap + 1));
       if (b.brick_of) dev_free(c, b.brick_of, sizeof(int32_t) * b.apron_cap);
       b.T9 = nullptr;
       b.brick_of = nullptr;
       b.apron_cap = 0;
       const int64_t cap = std::min<int64_t>(std::max<int64_t>(1, c->grid_bricks), na + na / 2 + 64);
-      ALLOC(c, b.T9, cap * 729);
+      ALLOC(c, b.T9, (cap + 1) * 729);
       ALLOC(c, b.brick_of, cap);
       b.apron_cap = cap;
     }
     if (!b.count) ALLOC(c, b.count, 1);
-    if (!b.work) ALLOC(c, b.work, 8);   // one counter per XCD
   }
   smooth_build(c, b, s, f);
   return hip_check(c, "smooth prepare");
@@ -1636,7 +1623,7 @@ int af_smooth_eval(af_ctx *c, const float *p, const float *q, int64_t n, const f
   int rc = smooth_prepare(c, s, f);
   if (rc != AF_OK) return rc;
   launch_smooth_eval(f, 256.0 / c->p.scale, p, q, n, samples, M, c_thr, tau_s, grad_s, s_out, dq,
-                     dp, c->sm.work, s);
+                     dp, s);
   c->last_stream = s;
   return hip_check(c, "smooth eval");
 }
@@ -1657,7 +1644,7 @@ int af_smooth_refine(af_ctx *c, const float *p, int64_t n_points, const float *q
   if (rc != AF_OK) return rc;
   hipEvent_t t0 = timing_mark(c, s);
   launch_smooth_refine(f, 256.0 / c->p.scale, p, n_points, q0, n_starts, samples, M, c_thr, tau_s,
-                       steps, eta, max_step, q_out, s_out, c->sm.work, s);
+                       steps, eta, max_step, q_out, s_out, s);
   hipEvent_t t1 = timing_mark(c, s);
   if (c->timing) timing_pair(c, ST_K_SMOOTH, t0, t1);
   c->last_stream = s;
@@ -1716,20 +1703,14 @@ int af_smooth_eval_static(af_ctx *c, const float *p, const float *q, int64_t n,
   if (!grid_covers(c))
     return fail(c, AF_EINVAL, "the brick grid must grow before this call (af_smooth_eval "
                               "or af_score_points grows it)");
-  // carve the scratch: every part 256-byte aligned
+  // What the map may need of the scratch is a fixed measure of its blocks and
+  // bricks (a little more than the parts below take).
   const int64_t nv = std::max<int64_t>(1, c->n_blocks * kBlockVox);
   const int64_t nb = std::max<int64_t>(1, c->grid_bricks);
   const int64_t na = std::max<int64_t>(1, std::min<int64_t>(8 * c->n_blocks, c->grid_bricks));
-  int64_t off = 0;
-  auto take = [&](int64_t bytes) {
-    const int64_t at = off;
-    off += (bytes + 255) & ~int64_t(255);
-    return at;
-  };
-  const int64_t oT = take(sizeof(float) * nv), oBid = take(sizeof(int32_t) * nb),
-                oBid9 = take(sizeof(int32_t) * nb), oOf = take(sizeof(int32_t) * na),
-                oT9 = take(sizeof(float) * 729 * na), oCount = take(sizeof(int32_t)),
-                oWork = take(sizeof(unsigned long long) * 8);
+  auto up = [](int64_t bytes) { return (bytes + 255) & ~int64_t(255); };
+  const int64_t off = up(sizeof(float) * nv) + 2 * up(sizeof(int32_t) * nb) + up(sizeof(int32_t) * na) +
+                      up(sizeof(float) * 729 * na) + 512;
   if (off > kStaticScratchBytes)
     return fail(c, AF_ENOMEM,
                 "the map needs %lld bytes of scratch (%lld blocks, %lld grid bricks); the static "
@@ -1738,18 +1719,21 @@ int af_smooth_eval_static(af_ctx *c, const float *p, const float *q, int64_t n,
                 (long long)kStaticScratchBytes);
   SmoothBuffers b;
   memset(&b, 0, sizeof(b));
-  b.T = (float *)(base + oT);
-  b.bid = (int32_t *)(base + oBid);
-  b.bid9 = (int32_t *)(base + oBid9);
-  b.brick_of = (int32_t *)(base + oOf);
-  b.T9 = (float *)(base + oT9);
-  b.count = (int32_t *)(base + oCount);
-  b.work = (unsigned long long *)(base + oWork);
+  uint8_t *at = base;   // every part 256-byte aligned
+  auto take = [&](int64_t bytes) {
+    uint8_t *part = at;
+    at += up(bytes);
+    return part;
+  };
+  b.count = (int32_t *)take(sizeof(int32_t));
+  b.bid9 = (int32_t *)take(sizeof(int32_t) * nb);
+  b.brick_of = (int32_t *)take(sizeof(int32_t) * na);
+  b.T9 = (float *)take(sizeof(float) * 729 * (na + 1));
   b.apron_cap = na;
   SmoothField f;
-  smooth_build(c, b, s, f);   // clears the count, the brick tables and the work counters first
+  smooth_build(c, b, s, f);   // clears the count and the brick table first
   launch_smooth_eval(f, 256.0 / c->p.scale, p, q, n, samples, M, c_thr, tau_s, grad_s, s_out, dq,
-                     dp, b.work, s);
+                     dp, s);
   c->last_stream = s;
   return hip_check(c, "smooth eval (static scratch)");
 }

@@ -378,8 +378,8 @@ void launch_incr_budget(const IncrDev &I, const ToolDev &t, hipStream_t s);
 
 // Smoothed clearance score.  T9: apron bricks of 9^3 floats (a brick's 8^3
 // voxels and the first layer of its +1 neighbours; tau where unmapped);
-// bid9: apron index of every brick of the dense grid (-1: no mapped voxel
-// within reach of a cell based in that brick).
+// bid9: apron index of every brick of the dense grid (0: no mapped voxel
+// within reach of a cell based in that brick; apron 0 holds tau throughout).
 struct SmoothField {
   const float *T9;
   const int32_t *bid9;
@@ -387,13 +387,10 @@ struct SmoothField {
   float tau;            // metres
 };
 struct SmoothBuffers {
-  float *T;             // [n_blocks * 512] per-voxel values (intermediate)
-  int32_t *bid;         // [grid bricks] block id or -1 (intermediate)
   int32_t *bid9;        // [grid bricks]
-  int32_t *brick_of;    // [apron_cap] grid brick of each apron
-  float *T9;            // [apron_cap * 729]
-  int32_t *count;       // aprons made
-  unsigned long long *work;   // [8] pairs handed out from each XCD's range
+  int32_t *brick_of;    // [apron_cap] grid brick of each apron but apron 0
+  float *T9;            // [(apron_cap + 1) * 729]
+  int32_t *count;       // aprons made, apron 0 included
   int64_t apron_cap;
 };
 void launch_smooth_prepare(const Params &p, MapDev m, int64_t n_blocks, GridDev g,
@@ -401,12 +398,11 @@ void launch_smooth_prepare(const Params &p, MapDev m, int64_t n_blocks, GridDev 
                            hipStream_t s);
 void launch_smooth_eval(const SmoothField &f, double v, const float *p, const float *q, int64_t n,
                         const float *samples, int32_t M, float c, float tau_s,
-                        const float *grad_s, float *s_out, float *dq, float *dp,
-                        unsigned long long *work, hipStream_t s);
+                        const float *grad_s, float *s_out, float *dq, float *dp, hipStream_t s);
 void launch_smooth_refine(const SmoothField &f, double v, const float *p, int64_t n_points,
                           const float *q0, int32_t n_starts, const float *samples, int32_t M,
                           float c, float tau_s, int32_t steps, float eta, float max_step,
-                          float *q_out, float *s_out, unsigned long long *work, hipStream_t s);
+                          float *q_out, float *s_out, hipStream_t s);
 // a recorded frame's end: status and block box into the sticky fields, and
 // the block and point counts into the snapshot the host reads
 void launch_stick_status(FrameCounters *c, const int32_t *n_blocks, const int32_t *n_points,
