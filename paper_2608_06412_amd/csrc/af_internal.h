@@ -464,12 +464,19 @@ void launch_normals(const Params &p, MapDev m, PointsDev pts, GridDev g,
                     int64_t n_points, hipStream_t s, bool dev_n = false);
 void launch_pca_axes(const int32_t *mom, int64_t n, int64_t *axes, int32_t *has,
                      hipStream_t s);
-void launch_mask(const Params &p, PointsDev pts, ToolDev t, GridDev g, int64_t n_points,
-                 hipStream_t s, bool dev_n = false);
 // Up to kMultiTools tools scored in one launch: their ids in the context's
 // device mirror of the tool table and the offsets of their begin arrays in
 // the launch's LDS copy (passed by value).
 constexpr int kMultiTools = 8;
+// Tools whose candidate masks are those of the tool being masked (the same
+// approach directions and arm samples): where their copies go.
+struct MaskCopies {
+  int32_t n;
+  uint64_t *mask[kMultiTools], *nearp[kMultiTools];
+  ScoreCounters *counters[kMultiTools];
+};
+void launch_mask(const Params &p, PointsDev pts, ToolDev t, GridDev g, int64_t n_points,
+                 hipStream_t s, bool dev_n = false, const MaskCopies *also = nullptr);
 struct ToolSet {
   int32_t n;
   int32_t id[kMultiTools];

@@ -581,16 +581,36 @@ __device__ inline uint32_t ent_code(const SwGrid &q, const SwFrame &f, uint32_t 
 // w0 - 1 as the previous launch wrote it: that orientation belongs to the run
 // of the last head before word w0, so it holds that head's candidate bit and
 // arm-sample result (every word but the last is full).
-template <int MW>
+//
+// PARTS > 1: that many waves share 64 points, each with every PARTS-th head of
+// a word (launch_mask says when).  `also`: tools whose masks are the same.
+__device__ inline uint64_t readfirst64(uint64_t v) {
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)v);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(v >> 32));
+  return ((uint64_t)hi << 32) | lo;
+}
+
+template <int MW, int PARTS>
 __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4)))
-k_mask_walk(Params p, PointsDev pts, ToolDev t, GridDev g, int64_t n, int w0, int mw) {
+k_mask_walk(Params p, PointsDev pts, ToolDev t, GridDev g, int64_t n, int w0, int mw,
+            MaskCopies also) {
   // n < 0: the point count on the device (recorded graphs, point lists)
   if (n < 0) n = pts.sel ? (int64_t)*pts.n_sel : (int64_t)*pts.n_points;
-  if ((int64_t)blockIdx.x * kThreads >= n) return;   // whole workgroup past the end
+  constexpr int kPoints = kThreads / PARTS;
+  static_assert(PARTS == 1 || kPoints == 64, "a wave per part");
+  const int64_t i0 = (int64_t)blockIdx.x * kPoints;
+  if (i0 >= n) return;   // whole workgroup past the end
+  const int part = PARTS == 1 ? 0 : __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kPoints));
+  const int row = threadIdx.x % kPoints;
   __shared__ double s_dir[3][64 * MW];
   __shared__ uint2 s_arm[3][64 * MW];
   __shared__ uint64_t s_run[64 * MW];
-  __shared__ uint64_t s_word[3][MW][kThreads];   // candidate word, plane 0, plane 1
+  __shared__ uint64_t s_word[3][MW][kPoints];    // candidate word, plane 0, plane 1
+  __shared__ uint64_t s_part[MW][PARTS];         // the heads of each part
+  if (PARTS > 1) {
+    if (threadIdx.x < MW * PARTS) s_part[threadIdx.x / PARTS][threadIdx.x % PARTS] = 0ull;
+    __syncthreads();
+  }
   for (int k = threadIdx.x; k < 64 * MW; k += kThreads) {
     const int w = w0 + (k >> 6), j = k & 63;
     const int kend = t.K - 64 * w < 64 ? t.K - 64 * w : 64;
@@ -607,16 +627,18 @@ k_mask_walk(Params p, PointsDev pts, ToolDev t, GridDev g, int64_t n, int w0, in
       for (int a = 0; a < 3; ++a) s_arm[a][k] = t.xent[b + a];
       if ((heads >> j) & 1ull) {
         const uint64_t above = j == 63 ? 0ull : heads & ~((2ull << j) - 1ull);
+        if (PARTS > 1)
+          atomicOr((unsigned long long *)&s_part[k >> 6]
+                                               [__popcll(heads & ((1ull << j) - 1ull)) % PARTS],
+                   1ull << j);
         run = (above ? (above & (~above + 1ull)) - 1ull : valid) & ~((1ull << j) - 1ull);
       }
     }
     s_run[k] = run;
   }
-#pragma unroll
-  for (int w = 0; w < MW; ++w)
-#pragma unroll
-    for (int c = 0; c < 3; ++c) s_word[c][w][threadIdx.x] = 0ull;
-  const int64_t jj = (int64_t)blockIdx.x * kThreads + threadIdx.x;
+  for (int e = threadIdx.x; e < 3 * MW * kPoints; e += kThreads) (&s_word[0][0][0])[e] = 0ull;
+  if (PARTS > 1) __syncthreads();   // s_part is read below
+  const int64_t jj = i0 + row;
   const bool act = jj < n;
   const int64_t i = pts.sel ? (act ? (int64_t)pts.sel[jj] : 0) : jj;
   const int hn = act ? pts.has_normal[i] : -1;
@@ -664,7 +686,8 @@ k_mask_walk(Params p, PointsDev pts, ToolDev t, GridDev g, int64_t n, int w0, in
   for (int w = 0; w < MW; ++w) {
     const int kend = t.K - 64 * (w0 + w) < 64 ? t.K - 64 * (w0 + w) : 64;
     const uint64_t valid = kend == 64 ? ~0ull : ((1ull << kend) - 1ull);
-    const uint64_t heads = ~t.same[w0 + w] & valid;
+    const uint64_t all = ~t.same[w0 + w] & valid;
+    const uint64_t heads = PARTS == 1 ? all : readfirst64(s_part[w][part]);
     cone[w] = hn == 0 ? heads : 0ull;
     if (hn > 0) {
       for (uint64_t rem = heads; rem; rem &= rem - 1ull) {
@@ -682,14 +705,19 @@ k_mask_walk(Params p, PointsDev pts, ToolDev t, GridDev g, int64_t n, int w0, in
   uint32_t pw[3] = {0u, 0u, 0u}, pb[3] = {0u, 0u, 0u};
   uint64_t prun = 0ull;   // run of the head whose words are in flight (0: none)
   int pword = 0;          // its word
+  // (the parts of a point share its words)
+  auto put = [&](int c, int w, uint64_t bits) {
+    if (PARTS == 1) s_word[c][w][row] |= bits;
+    else atomicOr((unsigned long long *)&s_word[c][w][row], (unsigned long long)bits);
+  };
   auto settle = [&]() {
     if (!prun) return;
     const uint32_t r = ((pw[0] >> pb[0]) & 3u) ? 1u
                        : ((pw[1] >> pb[1]) & 3u) ? 2u
                        : ((pw[2] >> pb[2]) & 3u) ? 3u
                                                  : 0u;
-    if (r & 1u) s_word[1][pword][threadIdx.x] |= prun;
-    if (r >> 1) s_word[2][pword][threadIdx.x] |= prun;
+    if (r & 1u) put(1, pword, prun);
+    if (r >> 1) put(2, pword, prun);
   };
   int cw = 0;
   uint64_t rem = cone[0];
@@ -722,7 +750,7 @@ k_mask_walk(Params p, PointsDev pts, ToolDev t, GridDev g, int64_t n, int w0, in
           cw3[a] = __builtin_amdgcn_raw_buffer_load_b32(q.pred, code_sw_at(q, f, s_arm[a][k], cb[a]),
                                                         0, 0);
         run = s_run[k];
-        s_word[0][cw][threadIdx.x] |= run;
+        put(0, cw, run);
       }
     }
     settle();   // the previous head's words, requested an iteration ago
@@ -735,73 +763,81 @@ k_mask_walk(Params p, PointsDev pts, ToolDev t, GridDev g, int64_t n, int w0, in
     pword = cw;
   }
   settle();
+  if (PARTS > 1) __syncthreads();
   // carries across words: orientations before a word's first head take the
   // candidate bit and arm-sample result of the last head before them
   unsigned long long cand = 0;
-  bool ok = false;
-  uint32_t nb = 0u;
-  if (w0 > 0 && act) {
-    ok = (t.mask[i * mw + w0 - 1] >> 63) != 0ull;
-    nb = (uint32_t)(t.nearp[i * 2 * mw + w0 - 1] >> 63) |
-         ((uint32_t)(t.nearp[i * 2 * mw + mw + w0 - 1] >> 63) << 1);
-  }
+  if (part == 0) {
+    bool ok = false;
+    uint32_t nb = 0u;
+    if (w0 > 0 && act) {
+      ok = (t.mask[i * mw + w0 - 1] >> 63) != 0ull;
+      nb = (uint32_t)(t.nearp[i * 2 * mw + w0 - 1] >> 63) |
+           ((uint32_t)(t.nearp[i * 2 * mw + mw + w0 - 1] >> 63) << 1);
+    }
 #pragma unroll
-  for (int w = 0; w < MW; ++w) {
-    const int kend = t.K - 64 * (w0 + w) < 64 ? t.K - 64 * (w0 + w) : 64;
-    const uint64_t valid = kend == 64 ? ~0ull : ((1ull << kend) - 1ull);
-    const uint64_t heads = ~t.same[w0 + w] & valid;
-    const uint64_t carry = heads ? ((heads & (~heads + 1ull)) - 1ull) : valid;
-    uint64_t word = s_word[0][w][threadIdx.x] | (ok ? carry : 0ull);
-    uint64_t pl0 = s_word[1][w][threadIdx.x] | ((nb & 1u) ? carry : 0ull);
-    uint64_t pl1 = s_word[2][w][threadIdx.x] | ((nb >> 1) ? carry : 0ull);
-    if (heads) {
-      const int jl = 63 - __clzll((long long)heads);   // the word's last head
-      ok = (word >> jl) & 1ull;
-      nb = (uint32_t)((pl0 >> jl) & 1ull) | ((uint32_t)((pl1 >> jl) & 1ull) << 1);
-    }
-    if (pts.sel) {
-      if (act) {
-        t.mask[i * mw + w0 + w] = word;
-        t.nearp[i * 2 * mw + w0 + w] = pl0;
-        t.nearp[i * 2 * mw + mw + w0 + w] = pl1;
+    for (int w = 0; w < MW; ++w) {
+      const int kend = t.K - 64 * (w0 + w) < 64 ? t.K - 64 * (w0 + w) : 64;
+      const uint64_t valid = kend == 64 ? ~0ull : ((1ull << kend) - 1ull);
+      const uint64_t heads = ~t.same[w0 + w] & valid;
+      const uint64_t carry = heads ? ((heads & (~heads + 1ull)) - 1ull) : valid;
+      uint64_t word = s_word[0][w][row] | (ok ? carry : 0ull);
+      uint64_t pl0 = s_word[1][w][row] | ((nb & 1u) ? carry : 0ull);
+      uint64_t pl1 = s_word[2][w][row] | ((nb >> 1) ? carry : 0ull);
+      if (heads) {
+        const int jl = 63 - __clzll((long long)heads);   // the word's last head
+        ok = (word >> jl) & 1ull;
+        nb = (uint32_t)((pl0 >> jl) & 1ull) | ((uint32_t)((pl1 >> jl) & 1ull) << 1);
       }
-    } else {
-      s_word[0][w][threadIdx.x] = word;
-      s_word[1][w][threadIdx.x] = pl0;
-      s_word[2][w][threadIdx.x] = pl1;
+      if (pts.sel) {
+        if (act) {
+          t.mask[i * mw + w0 + w] = word;
+          t.nearp[i * 2 * mw + w0 + w] = pl0;
+          t.nearp[i * 2 * mw + mw + w0 + w] = pl1;
+        }
+      } else {
+        s_word[0][w][row] = word;
+        s_word[1][w][row] = pl0;
+        s_word[2][w][row] = pl1;
+      }
+      cand += (unsigned long long)__popcll(word);
     }
-    cand += (unsigned long long)__popcll(word);
   }
   if (!pts.sel) {
     // rows of consecutive points are contiguous: written out together
     __syncthreads();
-    const int64_t i0 = (int64_t)blockIdx.x * kThreads;
-    const int np = n - i0 < kThreads ? (int)(n - i0) : kThreads;
-    if (MW == mw) {
-      for (int k = threadIdx.x; k < np * MW; k += kThreads)
-        t.mask[i0 * MW + k] = s_word[0][k % MW][k / MW];
-      for (int k = threadIdx.x; k < np * 2 * MW; k += kThreads) {
-        const int r = k / (2 * MW), c = k % (2 * MW);
-        t.nearp[i0 * 2 * MW + k] = c < MW ? s_word[1][c][r] : s_word[2][c - MW][r];
+    const int np = n - i0 < kPoints ? (int)(n - i0) : kPoints;
+    auto rows = [&](uint64_t *mask, uint64_t *nearp) {
+      if (MW == mw) {
+        for (int k = threadIdx.x; k < np * MW; k += kThreads)
+          mask[i0 * MW + k] = s_word[0][k % MW][k / MW];
+        for (int k = threadIdx.x; k < np * 2 * MW; k += kThreads) {
+          const int r = k / (2 * MW), c = k % (2 * MW);
+          nearp[i0 * 2 * MW + k] = c < MW ? s_word[1][c][r] : s_word[2][c - MW][r];
+        }
+      } else {   // this launch's words of each row
+        for (int k = threadIdx.x; k < np * MW; k += kThreads) {
+          const int r = k / MW, c = k % MW;
+          mask[(i0 + r) * mw + w0 + c] = s_word[0][c][r];
+          nearp[(i0 + r) * 2 * mw + w0 + c] = s_word[1][c][r];
+          nearp[(i0 + r) * 2 * mw + mw + w0 + c] = s_word[2][c][r];
+        }
       }
-    } else {   // this launch's words of each row
-      for (int k = threadIdx.x; k < np * MW; k += kThreads) {
-        const int r = k / MW, c = k % MW;
-        t.mask[(i0 + r) * mw + w0 + c] = s_word[0][c][r];
-        t.nearp[(i0 + r) * 2 * mw + w0 + c] = s_word[1][c][r];
-        t.nearp[(i0 + r) * 2 * mw + mw + w0 + c] = s_word[2][c][r];
-      }
-    }
+    };
+    rows(t.mask, t.nearp);
+    for (int u = 0; u < also.n; ++u) rows(also.mask[u], also.nearp[u]);
   }
+  if (part != 0) return;
   for (int off = 32; off >= 1; off >>= 1) {
     unsigned lo = __shfl_xor((unsigned)(cand & 0xffffffffu), off);
     unsigned hi = __shfl_xor((unsigned)(cand >> 32), off);
     cand += ((unsigned long long)hi << 32) | lo;
   }
-  if (lane_id() == 0 && cand)
-    atomicAdd(&t.counters->s[(blockIdx.x * kWaves + (threadIdx.x >> 6)) % kStatSlots]
-                   .candidate_tests,
-              cand);
+  if (lane_id() == 0 && cand) {
+    const int slot = (blockIdx.x * (kPoints / 64) + (threadIdx.x >> 6)) % kStatSlots;
+    atomicAdd(&t.counters->s[slot].candidate_tests, cand);
+    for (int u = 0; u < also.n; ++u) atomicAdd(&also.counters[u]->s[slot].candidate_tests, cand);
+  }
 }
 
 // Position of the r-th (1-based) set bit of m, or 64.
@@ -2337,22 +2373,38 @@ void launch_pca_axes(const int32_t *mom, int64_t n, int64_t *axes, int32_t *has,
                      0, s, mom, n, axes, has);
 }
 
-void launch_mask(const Params &p, PointsDev pts, ToolDev t, GridDev g, int64_t n,
-                 hipStream_t s, bool dev_n) {
-  int32_t mw = (t.K + 63) / 64;
-  if (n <= 0) return;
-  const dim3 grid((unsigned)((n + kThreads - 1) / kThreads));
+template <int PARTS>
+static void launch_mask_parts(const Params &p, PointsDev pts, ToolDev t, GridDev g, int64_t n,
+                              hipStream_t s, bool dev_n, const MaskCopies &also) {
+  const int32_t mw = (t.K + 63) / 64;
+  const dim3 grid((unsigned)((n * PARTS + kThreads - 1) / kThreads));
   const int64_t nn = dev_n ? (int64_t)-1 : n;
   // heads walked per lane, four mask words per launch (each launch after the
   // first reads the words the previous one wrote)
   for (int w0 = 0; w0 < mw; w0 += 4) {
-    switch (mw - w0 < 4 ? mw - w0 : 4) {
-      case 1: hipLaunchKernelGGL(k_mask_walk<1>, grid, dim3(kThreads), 0, s, p, pts, t, g, nn, w0, mw); break;
-      case 2: hipLaunchKernelGGL(k_mask_walk<2>, grid, dim3(kThreads), 0, s, p, pts, t, g, nn, w0, mw); break;
-      case 3: hipLaunchKernelGGL(k_mask_walk<3>, grid, dim3(kThreads), 0, s, p, pts, t, g, nn, w0, mw); break;
-      default: hipLaunchKernelGGL(k_mask_walk<4>, grid, dim3(kThreads), 0, s, p, pts, t, g, nn, w0, mw); break;
-    }
+    const auto fn = mw - w0 == 1   ? k_mask_walk<1, PARTS>
+                    : mw - w0 == 2 ? k_mask_walk<2, PARTS>
+                    : mw - w0 == 3 ? k_mask_walk<3, PARTS>
+                                   : k_mask_walk<4, PARTS>;
+    hipLaunchKernelGGL(fn, grid, dim3(kThreads), 0, s, p, pts, t, g, nn, w0, mw, also);
   }
+}
+
+// Below this many points a wave for every 64 points leaves the chip idle (16
+// waves a CU of 256 CUs), and each wave's walk through its heads is what the
+// call waits for: four waves share 64 points' heads.  Above it they only repeat
+// the points' set-up.  (18,000 points x 64 heads: 40 us with one wave, 16 with
+// four; 59,000 listed points 59 and 32; 310,000 x 97: 131 and 128; 1.15 M
+// 240 and 328.)  A list holds a part of the points that bound it.
+constexpr int64_t kMaskParts = 1 << 18;
+
+void launch_mask(const Params &p, PointsDev pts, ToolDev t, GridDev g, int64_t n,
+                 hipStream_t s, bool dev_n, const MaskCopies *also) {
+  if (n <= 0) return;
+  MaskCopies none;
+  none.n = 0;
+  const auto fn = n <= (pts.sel ? 4 * kMaskParts : kMaskParts) ? launch_mask_parts<4> : launch_mask_parts<1>;
+  fn(p, pts, t, g, n, s, dev_n, also ? *also : none);
 }
 
 int score_variants() { return kNumVariants; }
