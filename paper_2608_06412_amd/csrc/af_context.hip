@@ -1814,7 +1814,6 @@ int af_incremental_enable(af_ctx *c, int32_t tool_id, int32_t budget) {
     ALLOC(c, I.label, NP);
     ALLOC(c, I.n_sel, 1);
     ALLOC(c, I.bsum, (NP + 1023) / 1024);
-    ALLOC(c, I.hist, 2 * 65536);
     ALLOC(c, I.cand_h, 1024);
     ALLOC(c, I.cand_k, 1024);
     ALLOC(c, I.sampled, 256);

@@ -9,8 +9,8 @@
 //             time this fired: points labelled inaccessible are queued; new
 //             points are queued on first observation;
 //   sample    the 256 changed voxels (voxels that received a contribution)
-//             with the smallest SplitMix64 hash of key ^ frame * golden,
-//             found by two 16-bit radix histograms and one small sort;
+//             with the smallest SplitMix64 hash of key ^ frame * golden: those
+//             below a bound that some 512 meet, and one small sort;
 //             (ii) queues every point within 3v of a sampled voxel;
 //   select    queued points with W >= the confidence minimum, the first
 //             `budget` in point order (block counts, a scan, a ranked write);
@@ -26,6 +26,8 @@
 
 #include "af_internal.h"
 
+#include <algorithm>
+
 namespace af {
 namespace {
 
@@ -33,6 +35,7 @@ constexpr int kT = 256;
 constexpr int kSelT = 1024;         // points per selection block
 constexpr int kSample = 256;        // changed voxels sampled per frame
 constexpr int kCand = 1024;         // candidate capacity of the sample sort
+constexpr int kExpect = 512;        // candidates that the first bound lets through on average
 constexpr unsigned long long kGolden = 0x9E3779B97F4A7C15ull;
 
 // The output function of SplitMix64 (Steele, Lea and Flood).
@@ -58,31 +61,6 @@ __device__ inline int64_t voxel_key(const MapDev &m, int32_t addr) {
 
 __device__ inline unsigned long long sample_hash(int64_t key, int32_t frame) {
   return mix64((unsigned long long)key ^ ((unsigned long long)(int64_t)frame * kGolden));
-}
-
-// Workgroup counts of three per-thread flags (ballots, one exchange), added
-// to d0, d1, d2 by thread 0.
-template <int NT>
-__device__ inline void wg_count3(bool f0, bool f1, bool f2, int *d0, int *d1, int *d2) {
-  __shared__ int part[3][NT / 64];
-  const uint64_t b0 = __ballot(f0), b1 = __ballot(f1), b2 = __ballot(f2);
-  if ((threadIdx.x & 63) == 0) {
-    part[0][threadIdx.x >> 6] = __popcll(b0);
-    part[1][threadIdx.x >> 6] = __popcll(b1);
-    part[2][threadIdx.x >> 6] = __popcll(b2);
-  }
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    int t0 = 0, t1 = 0, t2 = 0;
-    for (int w = 0; w < NT / 64; ++w) {
-      t0 += part[0][w];
-      t1 += part[1][w];
-      t2 += part[2][w];
-    }
-    if (t0) atomicAdd(d0, t0);
-    if (t1) atomicAdd(d1, t1);
-    if (t2) atomicAdd(d2, t2);
-  }
 }
 
 // Workgroup sum of one value per thread, added to *dst by thread 0.
@@ -121,121 +99,66 @@ __global__ void __launch_bounds__(kT) k_incr_init(IncrDev I, int32_t n_c) {
 }
 
 // Triggers (i), (iii) and first observation; the point's S and W are kept
-// for the next frame.
-__global__ void __launch_bounds__(kT)
+// for the next frame.  The workgroups go round the points, so that the three
+// counters take an atomic each from a few hundred of them (one per 256 points
+// took turns at some 13 ns: 53 us for 940,000 points, now 26).
+constexpr int kTriggerGroups = 512;
+__global__ void __launch_bounds__(kSelT)
 k_incr_triggers(PointsDev pts, MapDev m, IncrDev I, int64_t n, int64_t seen, int moved) {
-  const int64_t i = (int64_t)blockIdx.x * kT + threadIdx.x;
   int c_new = 0, c_i = 0, c_iii = 0;
-  if (i < n) {
+  for (int64_t i = (int64_t)blockIdx.x * kSelT + threadIdx.x; i < n; i += (int64_t)gridDim.x * kSelT) {
     const int32_t addr = pts.addr[i];
     const int64_t S = addr >= 0 ? (int64_t)m.S[addr] : 0;
     const int64_t W = addr >= 0 ? (int64_t)m.W[addr] : 0;
     if (i >= seen) {   // first observation (points are appended, never removed)
       I.pending[i] = 1u;
-      c_new = 1;
+      ++c_new;
     } else {
+      bool t_i = false, t_iii = false;
       const int64_t Sp = I.S_prev[i], Wp = I.W_prev[i];
       if (Wp > 0 && W > 0) {
         int64_t d = S * Wp - Sp * W;
         d = d < 0 ? -d : d;
-        if (d > 512 * W * Wp) c_i = 1;   // |S/W - S'/W'| > 2v (2v = 512 units)
+        t_i = d > 512 * W * Wp;   // |S/W - S'/W'| > 2v (2v = 512 units)
       }
       const uint8_t lb = I.label[i];
       if (moved && (lb == AF_BLOCKED || lb == AF_NO_CANDIDATE)) {
         int32_t x, y, z;   // (iii) takes the points inside the sliding window
         unpack_key(pts.key[i], x, y, z);
-        c_iii = in_window(I, x, y, z);
+        t_iii = in_window(I, x, y, z);
       }
-      if (c_i || c_iii) I.pending[i] = 1u;
+      if (t_i || t_iii) I.pending[i] = 1u;
+      c_i += t_i;
+      c_iii += t_iii;
     }
     I.S_prev[i] = (int32_t)S;
     I.W_prev[i] = (uint16_t)W;
   }
-  wg_count3<kT>(c_new != 0, c_i != 0, c_iii != 0, &I.ctr->new_points, &I.ctr->trig_i,
-                 &I.ctr->trig_iii);
+  wg_add<kSelT>(c_new, &I.ctr->new_points);
+  wg_add<kSelT>(c_i, &I.ctr->trig_i);
+  wg_add<kSelT>(c_iii, &I.ctr->trig_iii);
 }
 
-// Histogram of the top 16 hash bits over the frame's changed voxels (level 0),
-// or of bits 32..47 over those in the chosen top bin (level 1).
-__global__ void __launch_bounds__(kT)
-k_incr_hist(MapDev m, const int32_t *changed, const FrameCounters *fc, int32_t frame, IncrDev I,
-            int level) {
-  const int64_t nc = fc->n_changed;
-  if (level == 1 && I.ctr->take_all) return;
-  for (int64_t j = (int64_t)blockIdx.x * kT + threadIdx.x; j < nc; j += (int64_t)gridDim.x * kT) {
-    const unsigned long long h = sample_hash(voxel_key(m, changed[j]), frame);
-    if (level == 0)
-      atomicAdd(&I.hist[h >> 48], 1u);
-    else if ((int)(h >> 48) == I.ctr->b1)
-      atomicAdd(&I.hist[65536 + ((h >> 32) & 0xffffu)], 1u);
-  }
+// The bound on the hashes of a frame's nc changed voxels (the hash maps keys
+// one to one, spread evenly): all of them where the sort takes all.
+__device__ inline unsigned long long sample_bound(int64_t nc) {
+  return nc <= kCand ? ~0ull : ~0ull / (unsigned long long)nc * kExpect;
 }
 
-// One workgroup: the smallest bin at which the running count of `hist`
-// reaches `need` (65536 bins, 64 per thread).
-__device__ inline void find_bin(const uint32_t *hist, int need, int &bin, int &below) {
-  __shared__ int sums[kSelT];
-  const int t = threadIdx.x;
-  int s = 0;
-  for (int k = 0; k < 64; ++k) s += (int)hist[64 * t + k];
-  sums[t] = s;
-  __syncthreads();
-  for (int off = 1; off < kSelT; off <<= 1) {
-    const int v = t >= off ? sums[t - off] : 0;
-    __syncthreads();
-    sums[t] += v;
-    __syncthreads();
-  }
-  const int incl = sums[t], excl = incl - s;
-  if (excl < need && incl >= need) {   // exactly one thread
-    int run = excl;
-    for (int k = 0; k < 64; ++k) {
-      const int c = (int)hist[64 * t + k];
-      if (run + c >= need) {
-        bin = 64 * t + k;
-        below = run;
-        break;
-      }
-      run += c;
-    }
-  }
-}
-
-__global__ void __launch_bounds__(kSelT) k_incr_pick(const FrameCounters *fc, IncrDev I, int level) {
-  IncrCounters *c = I.ctr;
-  if (level == 0) {
-    const int nc = fc->n_changed;
-    if (nc <= kSample) {
-      if (threadIdx.x == 0) c->take_all = 1;
-      return;
-    }
-    int bin = -1, below = 0;
-    find_bin(I.hist, kSample, bin, below);
-    if (bin >= 0) {
-      c->b1 = bin;
-      c->need = kSample - below;
-    }
-  } else {
-    if (c->take_all) return;
-    int bin = -1, below = 0;
-    find_bin(I.hist + 65536, c->need, bin, below);
-    if (bin >= 0) c->b2 = bin;
-  }
-}
-
-// Changed voxels whose hash is at most the selected prefix: the 256 smallest,
-// plus any sharing the last 32-bit prefix.
+// Changed voxels whose hash is within the bound.  The 256 smallest are among
+// them: some 512 are (a standard deviation of 23), which k_incr_sort checks.
+// (Two radix histograms over all the changed voxels and a search of their
+// bins took 107 us of a tree frame's 1.1 ms, this 9.)
 __global__ void __launch_bounds__(kT)
 k_incr_collect(MapDev m, const int32_t *changed, const FrameCounters *fc, int32_t frame,
                IncrDev I) {
   const int64_t nc = fc->n_changed;
-  const IncrCounters *c = I.ctr;
-  const int take_all = c->take_all, b1 = c->b1, b2 = c->b2;
+  if (nc > kCand && nc <= 2 * kCand) return;   // k_incr_sort goes through them itself
+  const unsigned long long bound = sample_bound(nc);
   for (int64_t j = (int64_t)blockIdx.x * kT + threadIdx.x; j < nc; j += (int64_t)gridDim.x * kT) {
     const int64_t key = voxel_key(m, changed[j]);
     const unsigned long long h = sample_hash(key, frame);
-    const int top = (int)(h >> 48), mid = (int)((h >> 32) & 0xffffu);
-    if (take_all || top < b1 || (top == b1 && mid <= b2)) {
+    if (h <= bound) {
       const int slot = atomicAdd(&I.ctr->n_cand, 1);
       if (slot < kCand) {
         I.cand_h[slot] = h;
@@ -246,13 +169,47 @@ k_incr_collect(MapDev m, const int32_t *changed, const FrameCounters *fc, int32_
 }
 
 // Sort the candidates by hash (bitonic, one workgroup) and keep the first 256.
-__global__ void __launch_bounds__(kSelT) k_incr_sort(IncrDev I) {
+// Where the bound did not let through between 256 and kCand of more (a chance
+// in 10^28), and for as few voxels as make going through them cheap, the
+// workgroup finds a bound that does by halving.
+__global__ void __launch_bounds__(kSelT)
+k_incr_sort(MapDev m, const int32_t *changed, const FrameCounters *fc, int32_t frame, IncrDev I) {
   __shared__ unsigned long long sh[kCand];
   __shared__ int64_t sk[kCand];
+  __shared__ int s_n;
   const int t = threadIdx.x;
-  const int n = I.ctr->n_cand < kCand ? I.ctr->n_cand : kCand;
-  sh[t] = t < n ? I.cand_h[t] : ~0ull;
-  sk[t] = t < n ? I.cand_k[t] : 0;
+  const int64_t nc = fc->n_changed;
+  int n = I.ctr->n_cand;
+  const bool ok = n <= kCand && (n >= kSample || n == nc);
+  sh[t] = ok && t < n ? I.cand_h[t] : ~0ull;
+  sk[t] = ok && t < n ? I.cand_k[t] : 0;
+  if (!ok) {
+    unsigned long long lo = 0ull, hi = ~0ull, bound = sample_bound(nc);
+    for (int turn = 0; turn < 130; ++turn) {   // (64 do: the hashes differ, so some bound fits)
+      if (t == 0) s_n = 0;
+      __syncthreads();
+      for (int64_t j = t; j < nc; j += kSelT) {
+        const int64_t key = voxel_key(m, changed[j]);
+        const unsigned long long h = sample_hash(key, frame);
+        if (h <= bound) {
+          const int slot = atomicAdd(&s_n, 1);
+          if (slot < kCand) {
+            sh[slot] = h;
+            sk[slot] = key;
+          }
+        }
+      }
+      __syncthreads();
+      n = s_n;
+      __syncthreads();
+      if (n >= kSample && n <= kCand) break;
+      if (n < kSample) lo = bound + 1ull;
+      else hi = bound - 1ull;
+      bound = lo + (hi - lo) / 2ull;
+    }
+    n = n < kCand ? n : kCand;
+    if (t >= n) sh[t] = ~0ull;
+  }
   __syncthreads();
   for (int k = 2; k <= kCand; k <<= 1)
     for (int j = k >> 1; j > 0; j >>= 1) {
@@ -299,7 +256,7 @@ __device__ inline bool selectable(const PointsDev &pts, const MapDev &m, const I
   return I.pending[i] != 0u && addr >= 0 && (int32_t)m.W[addr] >= min_w;
 }
 
-// Selection, pass 1: selectable and queued points per block of 1024.
+// Selection, pass 1: selectable (low half) and queued points per block of 1024.
 __global__ void __launch_bounds__(kSelT)
 k_incr_sel_count(PointsDev pts, MapDev m, IncrDev I, int64_t n, int32_t min_w) {
   const int64_t i = (int64_t)blockIdx.x * kSelT + threadIdx.x;
@@ -308,11 +265,10 @@ k_incr_sel_count(PointsDev pts, MapDev m, IncrDev I, int64_t n, int32_t min_w) {
   __shared__ int cnt;
   if (threadIdx.x == 0) cnt = 0;
   __syncthreads();
-  const unsigned long long b = __ballot(f);
-  if ((threadIdx.x & 63) == 0 && b) atomicAdd(&cnt, __popcll(b));
+  const int both = __popcll(__ballot(f)) + (__popcll(__ballot(q)) << 16);
+  if ((threadIdx.x & 63) == 0 && both) atomicAdd(&cnt, both);
   __syncthreads();
   if (threadIdx.x == 0) I.bsum[blockIdx.x] = cnt;
-  wg_add<kSelT>(q, &I.ctr->queued);
 }
 
 // Pass 2 (one workgroup): block offsets, the list length.
@@ -321,8 +277,12 @@ __global__ void __launch_bounds__(kSelT) k_incr_sel_scan(IncrDev I, int64_t nblk
   const int t = threadIdx.x;
   const int64_t per = (nblk + kSelT - 1) / kSelT;
   const int64_t lo = t * per < nblk ? t * per : nblk, hi = lo + per < nblk ? lo + per : nblk;
-  int s = 0;
-  for (int64_t b = lo; b < hi; ++b) s += I.bsum[b];
+  int s = 0, queued = 0;
+  for (int64_t b = lo; b < hi; ++b) {
+    s += I.bsum[b] & 0xffff;
+    queued += I.bsum[b] >> 16;
+  }
+  wg_add<kSelT>(queued, &I.ctr->queued);
   part[t] = s;
   __syncthreads();
   for (int off = 1; off < kSelT; off <<= 1) {
@@ -333,7 +293,7 @@ __global__ void __launch_bounds__(kSelT) k_incr_sel_scan(IncrDev I, int64_t nblk
   }
   int run = part[t] - s;
   for (int64_t b = lo; b < hi; ++b) {
-    const int c = I.bsum[b];
+    const int c = I.bsum[b] & 0xffff;
     I.bsum[b] = run;
     run += c;
   }
@@ -375,20 +335,33 @@ k_incr_sel_write(PointsDev pts, MapDev m, IncrDev I, int64_t n, int32_t min_w) {
 }
 
 // Raw collision count (body voxels with TSDF < r_c) of each listed point's
-// first free orientation; n_c for points without one.  Wave per point.
+// first free orientation; n_c for points without one.  A wave takes up to
+// eight points, a lane each, and goes through the accessible ones among them
+// with a lane per entry.  (A wave per point waited for three dependent reads
+// of each, mostly to find it blocked: 81 us for 242,000 points, 10,000 of them
+// accessible; now 35.)
 __global__ void __launch_bounds__(kT)
 k_incr_count(PointsDev pts, ToolDev t, GridDev g, IncrDev I, int32_t n_c) {
   const int n = *I.n_sel;
   const int lane = threadIdx.x & 63;
-  const int64_t nw = (int64_t)gridDim.x * (kT / 64);
-  for (int64_t j = ((int64_t)blockIdx.x * kT + threadIdx.x) >> 6; j < n; j += nw) {
-    const int32_t pi = I.sel[j];
-    int cnt = n_c;
-    if (t.label[pi] == AF_ACCESSIBLE) {
-      const int k = t.first_free[pi];
-      int32_t s[3];
-      unpack_key(pts.key[pi], s[0], s[1], s[2]);
-      cnt = 0;
+  const int nw = (int)gridDim.x * (kT / 64);
+  const int few = (n + nw - 1) / nw, per = few < 8 ? (few > 0 ? few : 1) : 8;
+  const int64_t wave = __builtin_amdgcn_readfirstlane((int)((blockIdx.x * kT + threadIdx.x) >> 6));
+  for (int64_t j0 = wave * per; j0 < n; j0 += (int64_t)nw * per) {
+    const int64_t j = j0 + lane;
+    const bool mine = lane < per && j < n;
+    const int32_t pi = mine ? I.sel[j] : 0;
+    const bool open = mine && t.label[pi] == AF_ACCESSIBLE;
+    const int first = open ? t.first_free[pi] : 0;
+    int32_t s[3] = {0, 0, 0};
+    if (open) unpack_key(pts.key[pi], s[0], s[1], s[2]);
+    int result = n_c;
+    for (uint64_t left = __ballot(open); left; left &= left - 1ull) {
+      const int l = __builtin_ctzll(left);
+      const int k = __builtin_amdgcn_readlane(first, l);
+      const int px = __builtin_amdgcn_readlane(s[0], l), py = __builtin_amdgcn_readlane(s[1], l),
+                pz = __builtin_amdgcn_readlane(s[2], l);
+      int cnt = 0;
       // a table lists 3 arm samples, then the body entries, then the corridor
       // entries (from far_begin): only the body range is visited
       const uint32_t eb = t.far_begin[k];
@@ -398,7 +371,7 @@ k_incr_count(PointsDev pts, ToolDev t, GridDev g, IncrDev I, int32_t n_c) {
         if (e < eb) {
           const uint32_t ent = t.entries[e];
           if (entry_cls(ent) == AF_CLS_BODY) {
-            const int x = s[0] + entry_x(ent), y = s[1] + entry_y(ent), z = s[2] + entry_z(ent);
+            const int x = px + entry_x(ent), y = py + entry_y(ent), z = pz + entry_z(ent);
             const int bx = (x >> 3) - g.g0[0], by = (y >> 3) - g.g0[1], bz = (z >> 3) - g.g0[2];
             if ((unsigned)bx < (unsigned)g.gd[0] && (unsigned)by < (unsigned)g.gd[1] &&
                 (unsigned)bz < (unsigned)g.gd[2]) {
@@ -410,8 +383,9 @@ k_incr_count(PointsDev pts, ToolDev t, GridDev g, IncrDev I, int32_t n_c) {
         }
         cnt += __popcll(__ballot(hit));
       }
+      result = lane == l ? cnt : result;
     }
-    if (lane == 0) I.score_new[j] = (uint8_t)cnt;
+    if (mine) I.score_new[j] = (uint8_t)result;
   }
 }
 
@@ -609,25 +583,21 @@ void launch_incr_frame_front(PointsDev pts, MapDev m, const IncrDev &I, const in
   hipLaunchKernelGGL(k_incr_fill, dim3(1), dim3(kT), 0, s, (uint32_t *)I.ctr,
                      (int64_t)(sizeof(IncrCounters) / 4), 0u);
   hipLaunchKernelGGL(k_incr_copy_int, dim3(1), dim3(1), 0, s, I.frame_budget, I.budget_dev);
-  hipLaunchKernelGGL(k_incr_fill, dim3(256), dim3(kT), 0, s, I.hist, (int64_t)2 * 65536, 0u);
   if (n_points > 0)
-    hipLaunchKernelGGL(k_incr_triggers, dim3(grid_of(n_points, kT)), dim3(kT), 0, s, pts, m, I,
-                       n_points, seen, moved ? 1 : 0);
+    hipLaunchKernelGGL(k_incr_triggers,
+                       dim3((unsigned)std::min<int64_t>(kTriggerGroups, (n_points + kSelT - 1) / kSelT)),
+                       dim3(kSelT), 0, s, pts, m, I, n_points, seen, moved ? 1 : 0);
   const dim3 wide(2048);
-  hipLaunchKernelGGL(k_incr_hist, wide, dim3(kT), 0, s, m, changed, fc, frame, I, 0);
-  hipLaunchKernelGGL(k_incr_pick, dim3(1), dim3(kSelT), 0, s, fc, I, 0);
-  hipLaunchKernelGGL(k_incr_hist, wide, dim3(kT), 0, s, m, changed, fc, frame, I, 1);
-  hipLaunchKernelGGL(k_incr_pick, dim3(1), dim3(kSelT), 0, s, fc, I, 1);
   hipLaunchKernelGGL(k_incr_collect, wide, dim3(kT), 0, s, m, changed, fc, frame, I);
-  hipLaunchKernelGGL(k_incr_sort, dim3(1), dim3(kSelT), 0, s, I);
+  hipLaunchKernelGGL(k_incr_sort, dim3(1), dim3(kSelT), 0, s, m, changed, fc, frame, I);
   hipLaunchKernelGGL(k_incr_neigh, dim3(kSample), dim3(384), 0, s, pts, I, n_points);
   launch_select(pts, m, I, n_points, min_w, s);
 }
 
 void launch_incr_frame_back(PointsDev pts, MapDev m, ToolDev t, GridDev g, const IncrDev &I,
                             int64_t n_points, int32_t n_c, hipStream_t s) {
-  hipLaunchKernelGGL(k_incr_count, dim3(grid_of(I.budget, kT / 64)), dim3(kT), 0, s, pts, t, g,
-                     I, n_c);
+  hipLaunchKernelGGL(k_incr_count, dim3((unsigned)std::min<int64_t>(2048, grid_of(I.budget, kT / 64))),
+                     dim3(kT), 0, s, pts, t, g, I, n_c);
   hipLaunchKernelGGL(k_incr_update, dim3(grid_of(I.budget, kT)), dim3(kT), 0, s, t, I, n_c);
   if (n_points > 0)
     hipLaunchKernelGGL(k_incr_labels, dim3(grid_of(n_points, kT)), dim3(kT), 0, s, pts, m, I,

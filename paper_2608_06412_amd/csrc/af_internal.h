@@ -312,7 +312,6 @@ void launch_normals_cached(const Params &p, MapDev m, PointsDev pts, GridDev g,
 struct IncrCounters {
   int32_t new_points, trig_i, trig_ii, trig_iii;
   int32_t sampled, n_cand, queued, selectable;
-  int32_t b1, b2, need, take_all;   // sample selection: top bin, second bin, count, all
 };
 struct IncrDev {
   uint8_t *best;          // [max_points] stored score; n_c = no free direction stored
@@ -327,7 +326,6 @@ struct IncrDev {
   int32_t *n_sel;
   int32_t *bsum;          // [ceil(max_points / 1024)] selection block counts / offsets
   uint8_t *score_new;     // [budget] raw collision count of this frame's evaluation
-  uint32_t *hist;         // [2 * 65536] sample histograms
   unsigned long long *cand_h;   // [1024] sample candidates: hash, key
   int64_t *cand_k;
   int64_t *sampled;       // [256] sampled changed voxels (keys)
