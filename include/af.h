@@ -339,10 +339,11 @@ int af_timing_read(af_ctx *ctx, af_timing *out, int reset);
 int af_score_tools(af_ctx *ctx, const int32_t *tool_ids, int32_t n_tools, void *stream);
 
 /* Scoring kernel configurations: "plain" (one orientation at a time, any K),
- * "swar" (candidate-parallel first entries, grid-relative lookups) and "near"
+ * "swar" (candidate-parallel first entries, grid-relative lookups), "near"
  * (arm samples taken from the mask pass), with unrolling, dynamic point
  * fetch, the 4^3-cell corridor skip ("coarse4") and the one-bit occupancy
- * plane ("bit") as options.  All give identical labels, first free
+ * plane ("bit") as options, and "chunk" (64 entries a step, the corridor's
+ * occupied cells naming the steps to read).  All give identical labels, first free
  * orientations and canonical counts; they differ in speed only.  A new
  * context uses af_score_variant_default(); configurations that need K <= 256
  * fall back to configuration 0 for larger K.  af_tune_score times every

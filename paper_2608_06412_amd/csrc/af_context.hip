@@ -31,6 +31,7 @@ struct af_ctx {
   int64_t grid_bricks;
   FrameCounters *counters;      // device
   FrameCounters *counters_host; // pinned
+  hipEvent_t ev_counters;       // a frame's counters have reached it
   std::vector<ToolDev> tools;
   std::vector<int64_t> tool_bytes;
   uint64_t *mask;               // shared candidate-mask scratch
@@ -454,6 +455,7 @@ int af_create(const af_config *cfg, af_ctx **out) {
   auto bail = [&](int rc) {
     for (void *q : c->allocs) hipFree(q);
     if (c->counters_host) hipHostFree(c->counters_host);
+    if (c->ev_counters) hipEventDestroy(c->ev_counters);
     delete c;
     return rc;
   };
@@ -508,6 +510,8 @@ int af_create(const af_config *cfg, af_ctx **out) {
   for (auto &t : c->tools) memset(&t, 0, sizeof(t));
   if (hipHostMalloc((void **)&c->counters_host, sizeof(FrameCounters)) != hipSuccess)
     return bail(AF_ENOMEM);
+  if (hipEventCreateWithFlags(&c->ev_counters, hipEventDisableTiming) != hipSuccess)
+    return bail(AF_EDEVICE);
   memset(c->counters_host, 0, sizeof(FrameCounters));
   if (hipMemset(m.h.keys, 0xff, sizeof(int64_t) * ((int64_t)m.h.mask + 1)) != hipSuccess ||
       hipMemset(q.h.keys, 0xff, sizeof(int64_t) * ((int64_t)q.h.mask + 1)) != hipSuccess ||
@@ -531,6 +535,7 @@ int af_destroy(af_ctx *c) {
   for (hipEvent_t e : c->ev_free) hipEventDestroy(e);
   for (void *q : c->allocs) hipFree(q);
   if (c->counters_host) hipHostFree(c->counters_host);
+  if (c->ev_counters) hipEventDestroy(c->ev_counters);
   delete c;
   return AF_OK;
 }
@@ -1023,7 +1028,27 @@ int af_integrate_frame(af_ctx *c, const float *xyz, int64_t n, const float origi
   if (thaw) launch_window_link(c->map, c->pts, c->n_points, wlo, whi, s);
   HIP_TRY(c, hipMemcpyAsync(c->counters_host, c->counters, offsetof(FrameCounters, fold),
                             hipMemcpyDeviceToHost, s));
-  HIP_TRY(c, hipStreamSynchronize(s));
+  // The grid has to cover the new blocks before the fold writes their bricks,
+  // so the host waits for the counters here.  What does not need the grid is
+  // queued before it waits, so the GPU does not (some 20 us a frame).  With a
+  // memory budget the frame stops here when the grid cannot grow, with nothing
+  // of it marked yet.
+  const bool ahead = c->cfg.hbm_budget == 0;
+  const int64_t touched = std::min<int64_t>(c->cfg.max_blocks, n * (kMaxSpan + kMaxBand));
+  hipEvent_t t1{};
+  auto front = [&](int64_t new_points) {
+    launch_touch_band(c->fargs, n, c->p, c->map, c->fs, c->counters, s);
+    launch_points_append(new_points, c->map, c->pts, c->fs, c->counters, c->fargs, s);
+    t1 = timing_mark(c, s);
+    launch_bins(c->fargs, n, c->p, c->map, c->pts, c->fs, c->counters, touched, s);
+  };
+  if (ahead) {
+    HIP_TRY(c, hipEventRecord(c->ev_counters, s));
+    front(n);
+    HIP_TRY(c, hipEventSynchronize(c->ev_counters));
+  } else {
+    HIP_TRY(c, hipStreamSynchronize(s));
+  }
   if ((rc = hip_check(c, "frame prep")) != AF_OK) return rc;
   FrameCounters h = *c->counters_host;
   if (h.n_new_blocks > 0 && !c->win_on) {   // (with a window the box is the window)
@@ -1034,15 +1059,16 @@ int af_integrate_frame(af_ctx *c, const float *xyz, int64_t n, const float origi
     c->have_bbox = true;
   }
   bool rebuilt = false;
-  if ((rc = ensure_grid(c, s, rebuilt, shift)) != AF_OK) return rc;
-  launch_touch_band(c->fargs, n, c->p, c->map, c->fs, c->counters, s);
-  launch_points_append(h.n_new_points, c->map, c->pts, c->fs, c->counters, c->fargs, s);
+  if ((rc = ensure_grid(c, s, rebuilt, shift)) != AF_OK) {
+    if (ahead) launch_bins_drop(c->map, c->fs, c->counters, s);
+    return rc;
+  }
+  if (!ahead) front(h.n_new_points);
   // new blocks take evicted ids first
   int64_t nb_after = std::min<int64_t>(
       (int64_t)h.blocks_before + std::max<int64_t>(0, (int64_t)h.n_new_blocks - h.free_before),
       c->cfg.max_blocks);
-  hipEvent_t t1 = timing_mark(c, s);
-  launch_integrate(c->fargs, n, c->p, c->map, c->pts, c->fs, c->counters, c->grid,
+  launch_fold(c->fargs, c->p, c->map, c->fs, c->counters, c->grid,
                    std::max<int64_t>(1, std::min<int64_t>(nb_after, n * (kMaxSpan + kMaxBand))), s);
   hipEvent_t t2 = timing_mark(c, s);
   if (rebuilt) launch_grid_rebuild(c->p, c->map, c->grid, nb_after, s);
@@ -1066,7 +1092,7 @@ int af_integrate_frame(af_ctx *c, const float *xyz, int64_t n, const float origi
   return AF_OK;
 }
 
-static int cached_normals(af_ctx *c, hipStream_t s);
+static int cached_normals(af_ctx *c, ScoreBegin &b, hipStream_t s);
 
 // Tools a windowed graph scores take the point list (reach of 255 voxels at most).
 static int window_tools_ok(af_ctx *c, const int32_t *ids, int32_t n) {
@@ -1142,13 +1168,15 @@ int af_score_points(af_ctx *c, int32_t tool_id, void *stream) {
   if (rc != AF_OK) return rc;
   if (c->win_on) return score_window(c, &tool_id, 1, s);
   hipEvent_t t0 = timing_mark(c, s);
-  HIP_TRY(c, hipMemsetAsync(t.counters, 0, sizeof(ScoreCounters), s));
+  ScoreBegin begin;
+  begin.n = 1;
+  begin.counters[0] = t.counters;
   hipEvent_t t1 = timing_mark(c, s);
-  if ((rc = cached_normals(c, s)) != AF_OK) return rc;
+  if ((rc = cached_normals(c, begin, s)) != AF_OK) return rc;
   hipEvent_t t2 = timing_mark(c, s);
   launch_mask(c->p, c->pts, t, c->grid, c->n_points, s);
   hipEvent_t t3 = timing_mark(c, s);
-  launch_score(c->p, c->pts, t, c->grid, c->n_points, c->score_variant, c->work, s);
+  launch_score(c->p, c->pts, t, c->grid, c->n_points, c->score_variant, c->work, s, false, true);
   hipEvent_t t4 = timing_mark(c, s);
   if (c->timing) {
     timing_pair(c, ST_SCORE, t0, t4);
@@ -1205,7 +1233,7 @@ static int sync_last(af_ctx *c);
 
 // Normals of every point, recomputing only the axes that points appended
 // since the last call can have changed.
-static int cached_normals(af_ctx *c, hipStream_t s) {
+static int cached_normals(af_ctx *c, ScoreBegin &b, hipStream_t s) {
   NormalCache &nc = c->ncache;
   if (!nc.axis || !nc.state || !nc.list || !nc.count) {   // (a failed call may have left a part)
     c->nc_seen = 0;
@@ -1225,6 +1253,9 @@ static int cached_normals(af_ctx *c, hipStream_t s) {
     nc.stale_words = 16 * c->grid_bricks;
     HIP_TRY(c, hipMemsetAsync(nc.stale, 0, sizeof(uint32_t) * nc.stale_words, s));
   }
+  b.count = nc.count;
+  b.work = c->work;
+  launch_score_begin(b, s);
   launch_normals_cached(c->p, c->map, c->pts, c->grid, nc, c->nc_seen, c->n_points, s);
   c->nc_seen = c->n_points;
   return AF_OK;
@@ -1263,17 +1294,18 @@ int af_score_tools(af_ctx *c, const int32_t *tool_ids, int32_t n_tools, void *st
   if ((rc = regrid(c, s)) != AF_OK) return rc;
   if (c->win_on) return score_window(c, tool_ids, n_tools, s);
   hipEvent_t t0 = timing_mark(c, s);
-  for (int32_t i = 0; i < n_tools; ++i)
-    HIP_TRY(c, hipMemsetAsync(host[i].counters, 0, sizeof(ScoreCounters), s));
+  ScoreBegin begin;
+  begin.n = n_tools;
+  for (int32_t i = 0; i < n_tools; ++i) begin.counters[i] = host[i].counters;
   hipEvent_t t1 = timing_mark(c, s);
-  if ((rc = cached_normals(c, s)) != AF_OK) return rc;
+  if ((rc = cached_normals(c, begin, s)) != AF_OK) return rc;
   hipEvent_t t2 = timing_mark(c, s);
   score_masks(c, set, host, c->n_points, s, false);
   hipEvent_t t3 = timing_mark(c, s);
   if (n_tools == 1)   // one tool: the single-tool kernel (same results)
-    launch_score(c->p, c->pts, host[0], c->grid, c->n_points, c->score_variant, c->work, s);
+    launch_score(c->p, c->pts, host[0], c->grid, c->n_points, c->score_variant, c->work, s, false, true);
   else
-    launch_score_multi(c->p, c->pts, c->tools_dev, host, set, c->grid, c->n_points, c->work, s);
+    launch_score_multi(c->p, c->pts, c->tools_dev, host, set, c->grid, c->n_points, c->work, s, false, true);
   hipEvent_t t4 = timing_mark(c, s);
   if (c->timing) {
     timing_pair(c, ST_SCORE, t0, t4);
@@ -1440,8 +1472,9 @@ static int graph_record(af_ctx *c, hipStream_t s) {
   launch_assign_blocks(c->map, c->fs, c->counters, c->fargs, cs);
   launch_touch_band(c->fargs, cap, c->p, c->map, c->fs, c->counters, cs);
   launch_points_append(cap, c->map, c->pts, c->fs, c->counters, c->fargs, cs);
-  launch_integrate(c->fargs, cap, c->p, c->map, c->pts, c->fs, c->counters, c->grid,
-                   std::min<int64_t>(c->cfg.max_blocks, cap * (kMaxSpan + kMaxBand)), cs);
+  const int64_t touched = std::min<int64_t>(c->cfg.max_blocks, cap * (kMaxSpan + kMaxBand));
+  launch_bins(c->fargs, cap, c->p, c->map, c->pts, c->fs, c->counters, touched, cs);
+  launch_fold(c->fargs, c->p, c->map, c->fs, c->counters, c->grid, touched, cs);
   launch_stick_status(c->counters, c->map.n_blocks, c->pts.n_points, cs);
   for (int32_t i = 0; i < n_tools; ++i)
     launch_zero_words(host[i].counters, sizeof(ScoreCounters), cs);

@@ -579,6 +579,12 @@ k_bin_fill(const FrameArgs *fa, Params p, MapDev m, PointsDev pts, FrameScratch 
   if (part == kParts - 1) point_view(r, fa->Q, fa->frame, p, pts, fs);
 }
 
+// Bins that will not be folded: the next frame's start from nothing again.
+__global__ void __launch_bounds__(kThreads) k_bin_drop(MapDev m, FrameScratch fs, FrameCounters *c) {
+  for (int i = blockIdx.x * kThreads + threadIdx.x; i < c->n_touched; i += gridDim.x * kThreads)
+    m.tpos[fs.touched[i]] = 0;
+}
+
 // A block's returns are dealt to its workgroup's eight waves; a wave takes up
 // to 64 of them at once, a lane each (its box of voxels in the block, the
 // return's place and direction), then goes through them one by one, a lane
@@ -1112,13 +1118,20 @@ void launch_assign_blocks(MapDev m, FrameScratch fs, FrameCounters *c, const Fra
   hipLaunchKernelGGL(k_assign_blocks, dim3(4096), dim3(kThreads), 0, s, m, fs, c, fa);
 }
 
-void launch_integrate(const FrameArgs *fa, int64_t nb, const Params &p, MapDev m, PointsDev pts,
-                      FrameScratch fs, FrameCounters *c, GridDev g, int64_t max_touched,
-                      hipStream_t s) {
+void launch_bins(const FrameArgs *fa, int64_t nb, const Params &p, MapDev m, PointsDev pts,
+                 FrameScratch fs, FrameCounters *c, int64_t max_touched, hipStream_t s) {
   hipLaunchKernelGGL(k_bin_place, dim3((unsigned)std::min<int64_t>(256, grid_for(max_touched))),
                      dim3(kThreads), 0, s, m, pts, fs, c);
   if (nb > 0)
     hipLaunchKernelGGL(k_bin_fill, dim3(part_grid(nb)), dim3(kPartThreads), 0, s, fa, p, m, pts, fs);
+}
+
+void launch_bins_drop(MapDev m, FrameScratch fs, FrameCounters *c, hipStream_t s) {
+  hipLaunchKernelGGL(k_bin_drop, dim3(256), dim3(kThreads), 0, s, m, fs, c);
+}
+
+void launch_fold(const FrameArgs *fa, const Params &p, MapDev m, FrameScratch fs, FrameCounters *c,
+                 GridDev g, int64_t max_touched, hipStream_t s) {
   int64_t wg = max_touched < 8192 ? max_touched : 8192;
   if (wg > 0) {
     if (fs.changed)

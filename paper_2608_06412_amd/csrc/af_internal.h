@@ -413,10 +413,13 @@ void launch_frame_prep(const float *xyz, FrameArgs *fa, const FrameArgs &fa_new,
                        hipStream_t s);
 void launch_assign_blocks(MapDev m, FrameScratch fs, FrameCounters *c, const FrameArgs *fa,
                           hipStream_t s);
-// Viewpoints, bins, fold and bricks; the frame's new ids become part of the map.
-void launch_integrate(const FrameArgs *fa, int64_t nb, const Params &p, MapDev m, PointsDev pts,
-                      FrameScratch fs, FrameCounters *c, GridDev g, int64_t max_touched,
-                      hipStream_t s);
+// Viewpoints and bins; the frame's new ids become part of the map.  Then the
+// fold and the bricks, or, where a frame ends before its fold, the bins dropped.
+void launch_bins(const FrameArgs *fa, int64_t nb, const Params &p, MapDev m, PointsDev pts,
+                 FrameScratch fs, FrameCounters *c, int64_t max_touched, hipStream_t s);
+void launch_fold(const FrameArgs *fa, const Params &p, MapDev m, FrameScratch fs, FrameCounters *c,
+                 GridDev g, int64_t max_touched, hipStream_t s);
+void launch_bins_drop(MapDev m, FrameScratch fs, FrameCounters *c, hipStream_t s);
 void launch_touch_band(const FrameArgs *fa, int64_t nb, const Params &p, MapDev m,
                        FrameScratch fs, FrameCounters *c, hipStream_t s);
 void launch_points_append(int64_t n_new, MapDev m, PointsDev pts, FrameScratch fs,
@@ -483,9 +486,18 @@ struct ToolSet {
 int multi_begin_capacity();
 void launch_score_multi(const Params &p, PointsDev pts, const ToolDev *tools_dev,
                         const ToolDev *host_tools, const ToolSet &set, GridDev g, int64_t n,
-                        unsigned *work, hipStream_t s, bool dev_n = false);
+                        unsigned *work, hipStream_t s, bool dev_n = false, bool begun = false);
+// What an eager scoring call counts in, cleared together: its tools' counters,
+// the normals' list length and the work counter (then `begun` below).
+struct ScoreBegin {
+  int32_t n;
+  ScoreCounters *counters[kMultiTools];
+  int32_t *count;
+  unsigned *work;
+};
+void launch_score_begin(const ScoreBegin &b, hipStream_t s);
 void launch_score(const Params &p, PointsDev pts, ToolDev t, GridDev g, int64_t n_points,
-                  int variant, unsigned *work, hipStream_t s, bool dev_n = false);
+                  int variant, unsigned *work, hipStream_t s, bool dev_n = false, bool begun = false);
 // One job of a cross-map scoring launch: every point of one context's map
 // (its point count read on the device) against one of its tools.
 struct ScoreJob {

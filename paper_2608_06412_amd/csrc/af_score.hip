@@ -2311,6 +2311,17 @@ k_pca_axes(const int32_t *mom, int64_t n, int64_t *axes, int32_t *has) {
 
 __global__ void k_zero(unsigned *w) { *w = 0u; }
 
+// Everything that an eager scoring call counts in (a workgroup per tool): one
+// launch where each counter had a fill of its own, some 4.5 us each.
+__global__ void __launch_bounds__(kThreads) k_score_begin(ScoreBegin b) {
+  uint32_t *w = (uint32_t *)b.counters[blockIdx.x];
+  for (unsigned k = threadIdx.x; k < sizeof(ScoreCounters) / 4; k += kThreads) w[k] = 0u;
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    *b.count = 0;
+    *b.work = 0u;
+  }
+}
+
 bool g_tables_ready = false;
 
 void init_tables() {
@@ -2337,11 +2348,14 @@ void init_tables() {
 
 }  // namespace
 
+void launch_score_begin(const ScoreBegin &b, hipStream_t s) {
+  hipLaunchKernelGGL(k_score_begin, dim3((unsigned)b.n), dim3(kThreads), 0, s, b);
+}
+
 void launch_normals_cached(const Params &p, MapDev m, PointsDev pts, GridDev g,
                            const NormalCache &nc, int64_t seen, int64_t n, hipStream_t s) {
   init_tables();
   if (n <= 0) return;
-  hipLaunchKernelGGL(k_zero, dim3(1), dim3(1), 0, s, (unsigned *)nc.count);
   const unsigned blocks = (unsigned)((n + kThreads - 1) / kThreads);
   const bool all = seen <= 0 || (n - seen) * 8 > n;   // most of the map is new
   const bool marked = !all && n > seen;
@@ -2425,8 +2439,9 @@ int multi_begin_capacity() { return kMultiBegin; }
 // like set.id) in one persistent launch.
 void launch_score_multi(const Params &p, PointsDev pts, const ToolDev *tools_dev,
                         const ToolDev *host_tools, const ToolSet &set, GridDev g, int64_t n,
-                        unsigned *work, hipStream_t s, bool dev_n) {
+                        unsigned *work, hipStream_t s, bool dev_n, bool begun) {
   if (n <= 0 || set.n <= 0) return;
+  if (!begun) hipLaunchKernelGGL(k_zero, dim3(1), dim3(1), 0, s, work);
   bool rel = true, chunk = chunk_grid_ok(g);
   for (int i = 0; i < set.n; ++i) {
     rel = rel && host_tools[i].rent != nullptr;
@@ -2434,7 +2449,6 @@ void launch_score_multi(const Params &p, PointsDev pts, const ToolDev *tools_dev
   }
   if (chunk) {
     const int64_t wg = std::min<int64_t>((int64_t)chunk_resident(256) * num_cu(), (n * set.n + 3) / 4);
-    hipLaunchKernelGGL(k_zero, dim3(1), dim3(1), 0, s, work);
     hipLaunchKernelGGL(k_score_chunk_multi<256>, dim3((unsigned)wg), dim3(256), 0, s, p, pts, tools_dev,
                        set, g, dev_n ? (int64_t)-1 : n, work);
     return;
@@ -2453,7 +2467,6 @@ void launch_score_multi(const Params &p, PointsDev pts, const ToolDev *tools_dev
   int64_t wg = (int64_t)per_cu * num_cu();
   const int64_t need = (n * set.n + 3) / 4;
   if (wg > need) wg = need;
-  hipLaunchKernelGGL(k_zero, dim3(1), dim3(1), 0, s, work);
   hipLaunchKernelGGL(fn, dim3((unsigned)wg), dim3(256), lds, s, p, pts, tools_dev, set, g,
                      dev_n ? (int64_t)-1 : n, work);
 }
@@ -2524,7 +2537,7 @@ bool score_variant_takes_list(int variant, const ToolDev &t) {
 }
 
 void launch_score(const Params &p, PointsDev pts, ToolDev t, GridDev g, int64_t n, int variant,
-                  unsigned *work, hipStream_t s, bool dev_n) {
+                  unsigned *work, hipStream_t s, bool dev_n, bool begun) {
   int32_t mw = (t.K + 63) / 64;
   if (n <= 0) return;
   variant = effective_variant(variant, t, &g);
@@ -2541,7 +2554,7 @@ void launch_score(const Params &p, PointsDev pts, ToolDev t, GridDev g, int64_t 
   int64_t wg = (int64_t)(v.chunk ? chunk_resident(v.threads) : g_resident[variant]) * num_cu();
   int64_t need = (n + nw - 1) / nw;
   if (wg > need) wg = need;
-  hipLaunchKernelGGL(k_zero, dim3(1), dim3(1), 0, s, work);
+  if (!begun) hipLaunchKernelGGL(k_zero, dim3(1), dim3(1), 0, s, work);
   hipLaunchKernelGGL(v.fn, dim3((unsigned)wg), dim3(v.threads), 0, s, p, pts, t, g,
                      dev_n ? (int64_t)-1 : n, mw, work);
 }
