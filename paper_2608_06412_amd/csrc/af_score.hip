@@ -556,8 +556,8 @@ __device__ inline uint32_t ent_code(const SwGrid &q, const SwFrame &f, uint32_t 
 }
 
 // Candidate masks (Section 3.4 "Approach directions"): one lane per point,
-// its normal and viewpoint vectors in registers (fp64, exact conversions of
-// integers).  For every candidate direction the lane also reads the
+// its normal and viewpoint vectors in registers (float, with a test in double
+// on the exact integers where float does not decide).  For every candidate direction the lane also reads the
 // direction's three arm samples (Section 3.4 "Arm path checking"; they depend
 // on the approach direction only, so orientations that share it share the
 // result) and records which one hits first, as two bit planes per mask word.
@@ -582,6 +582,10 @@ __device__ inline uint32_t ent_code(const SwGrid &q, const SwFrame &f, uint32_t 
 // of the last head before word w0, so it holds that head's candidate bit and
 // arm-sample result (every word but the last is full).
 //
+// The vector instructions of the tests bound it.  In float they take 6 a
+// viewpoint instead of some 9 and half the registers (five waves a SIMD where
+// LDS allows, four before): 1.15 M points x 64 heads 240 -> 215 us.
+//
 // PARTS > 1: that many waves share 64 points, each with every PARTS-th head of
 // a word (launch_mask says when).  `also`: tools whose masks are the same.
 __device__ inline uint64_t readfirst64(uint64_t v) {
@@ -591,7 +595,7 @@ __device__ inline uint64_t readfirst64(uint64_t v) {
 }
 
 template <int MW, int PARTS>
-__global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4)))
+__global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(5)))
 k_mask_walk(Params p, PointsDev pts, ToolDev t, GridDev g, int64_t n, int w0, int mw,
             MaskCopies also) {
   // n < 0: the point count on the device (recorded graphs, point lists)
@@ -602,7 +606,7 @@ k_mask_walk(Params p, PointsDev pts, ToolDev t, GridDev g, int64_t n, int w0, in
   if (i0 >= n) return;   // whole workgroup past the end
   const int part = PARTS == 1 ? 0 : __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kPoints));
   const int row = threadIdx.x % kPoints;
-  __shared__ double s_dir[3][64 * MW];
+  __shared__ float4 s_dir[64 * MW];
   __shared__ uint2 s_arm[3][64 * MW];
   __shared__ uint64_t s_run[64 * MW];
   __shared__ uint64_t s_word[3][MW][kPoints];    // candidate word, plane 0, plane 1
@@ -619,9 +623,7 @@ k_mask_walk(Params p, PointsDev pts, ToolDev t, GridDev g, int64_t n, int w0, in
       const uint64_t valid = kend == 64 ? ~0ull : ((1ull << kend) - 1ull);
       const uint64_t heads = ~t.same[w] & valid;
       const double *R = t.rot + 9 * (int64_t)(64 * w + j);
-      s_dir[0][k] = R[0];
-      s_dir[1][k] = R[3];
-      s_dir[2][k] = R[6];
+      s_dir[k] = make_float4((float)R[0], (float)R[3], (float)R[6], 0.0f);
       const uint32_t b = t.begin[64 * w + j];
 #pragma unroll
       for (int a = 0; a < 3; ++a) s_arm[a][k] = t.xent[b + a];
@@ -637,49 +639,76 @@ k_mask_walk(Params p, PointsDev pts, ToolDev t, GridDev g, int64_t n, int w0, in
     s_run[k] = run;
   }
   for (int e = threadIdx.x; e < 3 * MW * kPoints; e += kThreads) (&s_word[0][0][0])[e] = 0ull;
-  if (PARTS > 1) __syncthreads();   // s_part is read below
+  __syncthreads();   // s_dir and s_part are read below
   const int64_t jj = i0 + row;
   const bool act = jj < n;
   const int64_t i = pts.sel ? (act ? (int64_t)pts.sel[jj] : 0) : jj;
   const int hn = act ? pts.has_normal[i] : -1;
-  double n0 = 0, n1 = 0, n2 = 0, nn = 0;
-  double wx[kMaxVp], wy[kMaxVp], wz[kMaxVp], ww[kMaxVp];
+  // The tests in float: q = (u.d) |u.d| - c |u|^2 for a vector u and a unit
+  // direction d, within 2^-19 |u|^2 of its value (u and d round once per
+  // component, so u.d is within 2^-21.4 |u| and |u|^2 within 2^-21.7 of
+  // itself), compared with a margin m = 2^-17 |u|^2: above it yes, below -m no,
+  // and the test in double, on the exact integers, where it lies between.
+  float nx = 0, ny = 0, nz = 0, nt = __builtin_inff(), nm = 0;
+  float wx[kMaxVp], wy[kMaxVp], wz[kMaxVp], wt[kMaxVp], wm[kMaxVp];
+#pragma unroll
+  for (int j = 0; j < kMaxVp; ++j) {
+    wx[j] = wy[j] = wz[j] = wm[j] = 0.0f;
+    wt[j] = __builtin_inff();
+  }
   int nv = 0;
+  int32_t s[3] = {0, 0, 0};
   SwFrame f;
   f.Bp = f.rp = 0u;
   const SwGrid q = sw_grid(g);
   if (hn >= 0) {
     if (hn > 0) {
       const int32_t *nvp = pts.normal + 3 * i;
-      n0 = (double)nvp[0];
-      n1 = (double)nvp[1];
-      n2 = (double)nvp[2];
-      nn = (double)((int64_t)nvp[0] * nvp[0] + (int64_t)nvp[1] * nvp[1] +
-                    (int64_t)nvp[2] * nvp[2]);
+      nx = (float)nvp[0];
+      ny = (float)nvp[1];
+      nz = (float)nvp[2];
+      const float nn = __builtin_fmaf(nx, nx, __builtin_fmaf(ny, ny, nz * nz));
+      nt = (float)p.cos2 * nn;
+      nm = 0x1p-17f * nn;
     }
-    int32_t s[3];
     unpack_key(pts.key[i], s[0], s[1], s[2]);
     nv = pts.nvp[i];
 #pragma unroll
     for (int j = 0; j < kMaxVp; ++j) {
       if (j < nv) {
         const int32_t *V = pts.vp + (i * kMaxVp + j) * 3;
-        int64_t a0 = (int64_t)V[0] - (256 * (int64_t)s[0] + 128);
-        int64_t a1 = (int64_t)V[1] - (256 * (int64_t)s[1] + 128);
-        int64_t a2 = (int64_t)V[2] - (256 * (int64_t)s[2] + 128);
-        wx[j] = (double)a0;
-        wy[j] = (double)a1;
-        wz[j] = (double)a2;
-        ww[j] = (double)(a0 * a0 + a1 * a1 + a2 * a2);
-      } else {
-        wx[j] = wy[j] = wz[j] = ww[j] = 0.0;
+        // (coordinates are within 2^28, so their differences fit 32 bits)
+        wx[j] = (float)(V[0] - (256 * s[0] + 128));
+        wy[j] = (float)(V[1] - (256 * s[1] + 128));
+        wz[j] = (float)(V[2] - (256 * s[2] + 128));
+        const float ww = __builtin_fmaf(wx[j], wx[j], __builtin_fmaf(wy[j], wy[j], wz[j] * wz[j]));
+        wt[j] = (float)p.obs2 * ww;
+        wm[j] = 0x1p-17f * ww;
       }
     }
     f = sw_frame(g, q, s);
-  } else {
-#pragma unroll
-    for (int j = 0; j < kMaxVp; ++j) wx[j] = wy[j] = wz[j] = ww[j] = 0.0;
   }
+  auto cone_exact = [&](const double *R) {
+    const int32_t *nvp = pts.normal + 3 * i;
+    const double n0 = (double)nvp[0], n1 = (double)nvp[1], n2 = (double)nvp[2];
+    const double nn = (double)((int64_t)nvp[0] * nvp[0] + (int64_t)nvp[1] * nvp[1] +
+                               (int64_t)nvp[2] * nvp[2]);
+    const double dot = (n0 * R[0] + n1 * R[3]) + n2 * R[6];
+    return dot >= 0.0 && dot * dot >= p.cos2 * nn;
+  };
+  auto seen_exact = [&](const double *R) {
+    bool seen = false;
+    for (int v = 0; v < nv && !seen; ++v) {
+      const int32_t *V = pts.vp + (i * kMaxVp + v) * 3;
+      const int64_t a0 = (int64_t)V[0] - (256 * (int64_t)s[0] + 128);
+      const int64_t a1 = (int64_t)V[1] - (256 * (int64_t)s[1] + 128);
+      const int64_t a2 = (int64_t)V[2] - (256 * (int64_t)s[2] + 128);
+      const double wd = ((double)a0 * R[0] + (double)a1 * R[3]) + (double)a2 * R[6];
+      const double ww = (double)(a0 * a0 + a1 * a1 + a2 * a2);
+      seen = wd > 0.0 && wd * wd > p.obs2 * ww;
+    }
+    return seen;
+  };
   // normal cone of every head
   uint64_t cone[MW];
 #pragma unroll
@@ -689,17 +718,19 @@ k_mask_walk(Params p, PointsDev pts, ToolDev t, GridDev g, int64_t n, int w0, in
     const uint64_t all = ~t.same[w0 + w] & valid;
     const uint64_t heads = PARTS == 1 ? all : readfirst64(s_part[w][part]);
     cone[w] = hn == 0 ? heads : 0ull;
-    if (hn > 0) {
-      for (uint64_t rem = heads; rem; rem &= rem - 1ull) {
-        const int j = __ffsll((unsigned long long)rem) - 1;
-        const double *R = t.rot + 9 * (int64_t)(64 * (w0 + w) + j);
-        const double d0 = R[0], d1 = R[3], d2 = R[6];
-        const double dot = (n0 * d0 + n1 * d1) + n2 * d2;
-        if (dot >= 0.0 && dot * dot >= p.cos2 * nn) cone[w] |= 1ull << j;
+    for (uint64_t rem = heads; rem; rem &= rem - 1ull) {
+      const int j = __ffsll((unsigned long long)rem) - 1;
+      const float4 d = s_dir[64 * w + j];
+      const float dot = __builtin_fmaf(nx, d.x, __builtin_fmaf(ny, d.y, nz * d.z));
+      const float e = __builtin_fmaf(dot, __builtin_fabsf(dot), -nt);
+      bool in = e > nm;
+      const bool close = (__builtin_fabsf(e) <= nm) & (hn > 0);
+      if (__any(close)) {
+        if (close) in = cone_exact(t.rot + 9 * (int64_t)(64 * (w0 + w) + j));
       }
+      cone[w] |= in ? 1ull << j : 0ull;
     }
   }
-  __syncthreads();
   // A head's arm-sample words are requested in its iteration and decoded in
   // the next one, so their latency overlaps the next head's tests.
   uint32_t pw[3] = {0u, 0u, 0u}, pb[3] = {0u, 0u, 0u};
@@ -735,15 +766,16 @@ k_mask_walk(Params p, PointsDev pts, ToolDev t, GridDev g, int64_t n, int w0, in
     if (rem) {
       const int k = 64 * cw + __ffsll((unsigned long long)rem) - 1;
       rem &= rem - 1ull;
-      const double d0 = s_dir[0][k], d1 = s_dir[1][k], d2 = s_dir[2][k];
-      bool seen = false;
+      const float4 d = s_dir[k];
+      bool seen = false, close = false;
 #pragma unroll
       for (int v = 0; v < kMaxVp; ++v) {
-        if (v < nv && !seen) {
-          double wd = (wx[v] * d0 + wy[v] * d1) + wz[v] * d2;
-          seen = wd > 0.0 && wd * wd > p.obs2 * ww[v];
-        }
+        const float wd = __builtin_fmaf(wx[v], d.x, __builtin_fmaf(wy[v], d.y, wz[v] * d.z));
+        const float e = __builtin_fmaf(wd, __builtin_fabsf(wd), -wt[v]);
+        seen |= e > wm[v];
+        close |= __builtin_fabsf(e) <= wm[v];
       }
+      if (close & !seen) seen = seen_exact(t.rot + 9 * (int64_t)(64 * w0 + k));
       if (seen) {
 #pragma unroll
         for (int a = 0; a < 3; ++a)
@@ -2313,7 +2345,7 @@ __global__ void k_zero(unsigned *w) { *w = 0u; }
 
 // Everything that an eager scoring call counts in (a workgroup per tool): one
 // launch where each counter had a fill of its own, some 4.5 us each.
-__global__ void __launch_bounds__(kThreads) k_score_begin(ScoreBegin b) {
+__global__ void __launch_bounds__(kThreads) k_clear_counts(ScoreBegin b) {
   uint32_t *w = (uint32_t *)b.counters[blockIdx.x];
   for (unsigned k = threadIdx.x; k < sizeof(ScoreCounters) / 4; k += kThreads) w[k] = 0u;
   if (blockIdx.x == 0 && threadIdx.x == 0) {
@@ -2349,7 +2381,7 @@ void init_tables() {
 }  // namespace
 
 void launch_score_begin(const ScoreBegin &b, hipStream_t s) {
-  hipLaunchKernelGGL(k_score_begin, dim3((unsigned)b.n), dim3(kThreads), 0, s, b);
+  hipLaunchKernelGGL(k_clear_counts, dim3((unsigned)b.n), dim3(kThreads), 0, s, b);
 }
 
 void launch_normals_cached(const Params &p, MapDev m, PointsDev pts, GridDev g,
