@@ -2300,6 +2300,8 @@ const ScoreVariant kVariants[] = {
     {k_score_near<256, 1, 8, 2, 1, 0, 2, 1>, 256, "near wg256 unroll1 dyn8 coarse4 bit prefix2 rel", kNearK, 1},
     {k_score_chunk<256, 0>, 256, "chunk wg256", kNearK, 1, nullptr, 1},
     {k_score_chunk<1024, 1>, 1024, "chunk wg1024 lds1", kLfK, 1, "chunk wg256", 1},
+    {k_score_chunk<512, 0>, 512, "chunk wg512", kNearK, 1, nullptr, 1},
+    {k_score_chunk<1024, 0>, 1024, "chunk wg1024", kNearK, 1, nullptr, 1},
 };
 constexpr int kChunkElse = 6;   // where the chunk scan cannot run
 constexpr int kNumVariants = (int)(sizeof(kVariants) / sizeof(kVariants[0]));
