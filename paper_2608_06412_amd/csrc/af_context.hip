@@ -29,6 +29,7 @@ struct af_ctx {
   FrameScratch fs;
   GridDev grid;
   int64_t grid_bricks;
+  int32_t grid_margin;          // bricks of margin the grid was made with
   FrameCounters *counters;      // device
   FrameCounters *counters_host; // pinned
   hipEvent_t ev_counters;       // a frame's counters have reached it
@@ -246,9 +247,14 @@ static bool grid_covers(const af_ctx *c) {
 
 int ensure_grid(af_ctx *c, hipStream_t s, bool &rebuilt, bool force = false) {
   rebuilt = false;
-  if (!force && grid_covers(c)) return AF_OK;
   const int32_t need = grid_margin_need(c);
   GridDev &g = c->grid;
+  if (!force && grid_covers(c)) {
+    // (a tool loaded since may reach further: from now on a recorded frame's
+    // block that comes nearer to the border than that is reported)
+    g.margin = std::max(c->grid_margin, need);
+    return AF_OK;
+  }
   GridDev ng;
   memset(&ng, 0, sizeof(ng));
   int64_t nb = 1;
@@ -277,6 +283,7 @@ int ensure_grid(af_ctx *c, hipStream_t s, bool &rebuilt, bool force = false) {
     ng.occ4 = g.occ4;
     ng.occ1 = g.occ1;
     c->grid = ng;
+    c->grid_margin = need;
     launch_grid_fill(c->grid, s);
     for (const ToolDev &t : c->tools)
       if (t.entries && launch_table_grid(t, c->grid, s) != 0) return hip_check(c, "table grid");
@@ -298,6 +305,7 @@ int ensure_grid(af_ctx *c, hipStream_t s, bool &rebuilt, bool force = false) {
   ALLOC(c, ng.occ4, nb);
   ALLOC(c, ng.occ1, nb * 16);
   c->grid = ng;
+  c->grid_margin = need;
   c->grid_bricks = nb;
   launch_grid_fill(c->grid, s);
   for (const ToolDev &t : c->tools)

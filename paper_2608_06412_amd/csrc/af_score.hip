@@ -1674,9 +1674,7 @@ struct ChunkAcc {
 // registers.)
 struct ChunkGrid {
   const char *occ1, *occ4;
-  uint32_t nbricks;
   uint32_t gx, gxy;
-  int32_t g0[3];
 };
 struct ChunkTool {
   __amdgpu_buffer_rsrc_t tab;                              // ToolDev::pent
@@ -1689,10 +1687,8 @@ __device__ inline ChunkGrid chunk_grid(const GridDev &g) {
   ChunkGrid q;
   q.occ1 = (const char *)g.occ1;
   q.occ4 = (const char *)g.occ4;
-  q.nbricks = (uint32_t)g.gd[0] * (uint32_t)g.gd[1] * (uint32_t)g.gd[2];
   q.gx = (uint32_t)g.gd[0];
   q.gxy = (uint32_t)g.gd[0] * (uint32_t)g.gd[1];
-  for (int a = 0; a < 3; ++a) q.g0[a] = g.g0[a];
   return q;
 }
 
@@ -1708,10 +1704,14 @@ __device__ inline ChunkTool chunk_tool(const Params &p, const ToolDev &t) {
   return c;
 }
 
-// The plane seen from one point.
+// The plane seen from one point.  A point that lies nearer to the grid's border
+// than the tool reaches, or outside (a recorded frame reports such a block, and
+// scores its points all the same), sees no plane: its reads give 0 and touch no
+// memory.
 struct ChunkFrame {
   __amdgpu_buffer_rsrc_t occ;   // the one-bit plane from the point's brick on (less the bias)
   int32_t base;                 // that brick
+  uint32_t bricks;              // from there to the plane's end (0: no plane)
   uint32_t r;                   // the point's place in its brick, in the entry's fields
 };
 
@@ -1783,9 +1783,10 @@ __device__ inline uint32_t wave_or(uint32_t x) {
 // bricks, 96 more than the entries'.)
 __device__ inline uint64_t chunk_groups(const ChunkTool &t, const ChunkGrid &q, const ChunkFrame &f,
                                         uint32_t first, uint32_t n) {
-  const int32_t base = f.base - 96 * (int32_t)(1u + q.gx + q.gxy);
+  const uint32_t more_bias = 96u * (1u + q.gx + q.gxy);
   const __amdgpu_buffer_rsrc_t occ4 = __builtin_amdgcn_make_buffer_rsrc(
-      (void *)(q.occ4 + base), (short)0, (int)(q.nbricks - (uint32_t)base), 0x00020000);
+      (void *)(q.occ4 + (f.base - (int32_t)more_bias)), (short)0,
+      (int)(f.bricks ? f.bricks + more_bias : 0u), 0x00020000);
   const uint32_t lane = (uint32_t)lane_id();
   const uint32_t r4 = (f.r >> 2) & 0x00401001u;   // the point's cell parities, in the cells' fields
   uint32_t glo = 0u, ghi = 0u;
@@ -1837,17 +1838,18 @@ __device__ inline uint64_t bpermute64(uint64_t v, int lane) {
 }
 
 // One confident point: its label and first free orientation (-1: none).
-// r, base: its place in the brick, its brick less the entries' bias.  LF:
-// s_first holds the first chunk of every orientation (K <= kLfK).
+// r, base, bricks: its place in the brick, its brick less the entries' bias,
+// and the bricks from there on (see ChunkFrame).  LF: s_first holds the first chunk of every orientation (K <= kLfK).
 template <int LF>
 __device__ inline uint32_t chunk_point(const ChunkTool &t, const ChunkGrid &q, uint32_t r,
-                                       int32_t base, uint64_t words, int lane, ChunkAcc &acc,
-                                       const uint32_t *s_first, int32_t &ff) {
+                                       int32_t base, uint32_t bricks, uint64_t words, int lane,
+                                       ChunkAcc &acc, const uint32_t *s_first, int32_t &ff) {
   ChunkFrame f;
   f.r = r;
   f.base = base;
+  f.bricks = bricks;
   f.occ = __builtin_amdgcn_make_buffer_rsrc((void *)(q.occ1 + (int64_t)base * 64), (short)0,
-                                            (int)((q.nbricks - (uint32_t)base) << 6), 0x00020000);
+                                            (int)(bricks << 6), 0x00020000);
   asm volatile("" : "+v"(f.r));
   const int lane4 = lane << 2;
   auto chunk_at = [&](uint32_t c) {
@@ -1968,8 +1970,9 @@ __device__ inline uint32_t chunk_point(const ChunkTool &t, const ChunkGrid &q, u
 // of dependent reads; labels are written together.
 template <int LF>
 __device__ inline void chunk_batch(const PointsDev &pts, const ToolDev &t, const ChunkTool &ct,
-                                   const ChunkGrid &q, int64_t first, int64_t stride, int count,
-                                   int lane, ChunkAcc &acc, const uint32_t *s_first) {
+                                   const GridDev &g, const ChunkGrid &q, int64_t first,
+                                   int64_t stride, int count, int lane, ChunkAcc &acc,
+                                   const uint32_t *s_first) {
   const int64_t at = first + (lane < count ? lane : 0) * stride;
   const int32_t pi = pts.sel ? pts.sel[at] : (int32_t)at;
   const int32_t hn = pts.has_normal[pi];
@@ -1977,8 +1980,15 @@ __device__ inline void chunk_batch(const PointsDev &pts, const ToolDev &t, const
   unpack_key(pts.key[pi], s[0], s[1], s[2]);
   const uint32_t r = (uint32_t)(s[0] & 7) | ((uint32_t)(s[1] & 7) << 12) | ((uint32_t)(s[2] & 7) << 22);
   constexpr int bias = 32;   // the entries' bias, in bricks
-  const int32_t base = ((s[0] >> 3) - q.g0[0] - bias) + (int32_t)q.gx * ((s[1] >> 3) - q.g0[1] - bias) +
-                       (int32_t)q.gxy * ((s[2] >> 3) - q.g0[2] - bias);
+  const int need = (t.reach + 7) / 8;   // bricks an entry, and a cell, can lie away
+  int32_t b3[3];
+  bool inside = true;
+  for (int a = 0; a < 3; ++a) {
+    b3[a] = (s[a] >> 3) - g.g0[a];
+    inside = inside & (b3[a] >= need) & (b3[a] < g.gd[a] - need);
+  }
+  const int32_t base = (b3[0] - bias) + (int32_t)q.gx * (b3[1] - bias) + (int32_t)q.gxy * (b3[2] - bias);
+  const uint32_t bricks = inside ? q.gxy * (uint32_t)g.gd[2] - (uint32_t)base : 0u;
   uint32_t out = 0xffff0000u;   // this lane's point: label | first free << 16
   uint64_t next = chunk_words(t, ct.mw, __builtin_amdgcn_readlane(pi, 0), lane);
   for (int b = 0; b < count; ++b) {
@@ -1988,7 +1998,9 @@ __device__ inline void chunk_batch(const PointsDev &pts, const ToolDev &t, const
       int32_t ff;
       const uint32_t label =
           chunk_point<LF>(ct, q, (uint32_t)__builtin_amdgcn_readlane((int)r, b),
-                          __builtin_amdgcn_readlane(base, b), words, lane, acc, s_first, ff);
+                          __builtin_amdgcn_readlane(base, b),
+                          (uint32_t)__builtin_amdgcn_readlane((int)bricks, b), words, lane, acc,
+                          s_first, ff);
       out = lane == b ? label | ((uint32_t)ff << 16) : out;
     }
   }
@@ -2061,7 +2073,7 @@ k_score_chunk(Params p, PointsDev pts, ToolDev t, GridDev g, int64_t n, int32_t 
   ChunkAcc a{};
   chunk_deal(n, (int64_t)gridDim.x * NW, work, wave, lane,
              [&](int64_t first, int64_t stride, int count) {
-               chunk_batch<LF>(pts, t, ct, q, first, stride, count, lane, a, s_first);
+               chunk_batch<LF>(pts, t, ct, g, q, first, stride, count, lane, a, s_first);
                if (a.look > (1u << 30)) chunk_flush(sc, a, lane);
              });
   chunk_flush(sc, a, lane);
@@ -2219,7 +2231,8 @@ k_score_chunk_multi(Params p, PointsDev pts, const ToolDev *__restrict__ tools, 
                  const ChunkTool ct = chunk_tool(p, t);
                  const int64_t here = ((int64_t)(ti + 1) * n - first + stride - 1) / stride;
                  const int c = __builtin_amdgcn_readfirstlane(here < count ? (int)here : count);
-                 chunk_batch<0>(pts, t, ct, q, first - (int64_t)ti * n, stride, c, lane, a, nullptr);
+                 chunk_batch<0>(pts, t, ct, g, q, first - (int64_t)ti * n, stride, c, lane, a,
+                                nullptr);
                  if (a.look > (1u << 30)) chunk_flush(t.counters->s[slot], a, lane);
                  first += c * stride;
                  count -= c;
@@ -2263,7 +2276,8 @@ k_score_chunk_jobs(const ScoreJob *__restrict__ jobs, int32_t n_jobs, unsigned *
                  const ChunkGrid q = chunk_grid(jb.g);
                  const int64_t here = (s_start[ji + 1] - first + stride - 1) / stride;
                  const int c = __builtin_amdgcn_readfirstlane(here < count ? (int)here : count);
-                 chunk_batch<0>(jb.pts, jb.t, ct, q, first - s_start[ji], stride, c, lane, a, nullptr);
+                 chunk_batch<0>(jb.pts, jb.t, ct, jb.g, q, first - s_start[ji], stride, c, lane, a,
+                                nullptr);
                  if (a.look > (1u << 30)) chunk_flush(jb.t.counters->s[slot], a, lane);
                  first += c * stride;
                  count -= c;
