@@ -148,15 +148,21 @@ void dev_free(af_ctx *c, void *p, int64_t bytes) {
 }
 
 // The tools' chunk tables only make scoring faster: an allocation that does
-// not fit otherwise takes their room.
+// not fit otherwise takes their room.  So any allocation can change c->tools:
+// a call that allocates copies its tools after that (toolset_tools).
 bool drop_chunks(af_ctx *c) {
   bool any = false;
-  for (ToolDev &t : c->tools) {
+  for (size_t i = 0; i < c->tools.size(); ++i) {
+    ToolDev &t = c->tools[i];
     if (!t.pent) continue;
-    dev_free(c, t.pent, chunk_bytes(t));
-    dev_free(c, t.pmeta, sizeof(uint4) * t.K);
+    if (!any) hipDeviceSynchronize();   // (a launch in flight may read them)
+    uint32_t *const pent = t.pent;
+    uint4 *const pmeta = t.pmeta;
     t.pent = nullptr;
     t.pmeta = nullptr;
+    hipMemcpy(&c->tools_dev[i], &t, sizeof(ToolDev), hipMemcpyHostToDevice);
+    dev_free(c, pent, chunk_bytes(t));
+    dev_free(c, pmeta, sizeof(uint4) * t.K);
     any = true;
   }
   if (any) c->graph_stale = true;
@@ -1200,7 +1206,7 @@ int af_score_points(af_ctx *c, int32_t tool_id, void *stream) {
 // The tool set of one multi-tool launch: ids checked, LDS offsets, and each
 // tool given its own mask buffers (masks of every tool must coexist).
 static int make_toolset(af_ctx *c, const int32_t *tool_ids, int32_t n_tools, ToolSet &set,
-                        ToolDev *host, bool own_buffers = true) {
+                        bool own_buffers = true) {
   if (!tool_ids || n_tools < 1 || n_tools > kMultiTools)
     return fail(c, AF_EINVAL, "n_tools must be 1..%d", kMultiTools);
   memset(&set, 0, sizeof(set));
@@ -1232,9 +1238,14 @@ static int make_toolset(af_ctx *c, const int32_t *tool_ids, int32_t n_tools, Too
       c->own_mask[id] = 1;
       HIP_TRY(c, hipMemcpy(&c->tools_dev[id], &t, sizeof(ToolDev), hipMemcpyHostToDevice));
     }
-    host[i] = t;
   }
   return AF_OK;
+}
+
+// Its tools as the launches take them, after the last allocation before those
+// (see drop_chunks).
+static void toolset_tools(const af_ctx *c, const ToolSet &set, ToolDev *host) {
+  for (int32_t i = 0; i < set.n; ++i) host[i] = c->tools[set.id[i]];
 }
 
 static int sync_last(af_ctx *c);
@@ -1297,16 +1308,17 @@ int af_score_tools(af_ctx *c, const int32_t *tool_ids, int32_t n_tools, void *st
   if (c->graph_dirty && (rc = graph_settle(c)) != AF_OK) return rc;
   ToolSet set;
   ToolDev host[kMultiTools];
-  if ((rc = make_toolset(c, tool_ids, n_tools, set, host, !c->win_on)) != AF_OK) return rc;
+  if ((rc = make_toolset(c, tool_ids, n_tools, set, !c->win_on)) != AF_OK) return rc;
   hipStream_t s = (hipStream_t)stream;
   if ((rc = regrid(c, s)) != AF_OK) return rc;
   if (c->win_on) return score_window(c, tool_ids, n_tools, s);
   hipEvent_t t0 = timing_mark(c, s);
   ScoreBegin begin;
   begin.n = n_tools;
-  for (int32_t i = 0; i < n_tools; ++i) begin.counters[i] = host[i].counters;
+  for (int32_t i = 0; i < n_tools; ++i) begin.counters[i] = c->tools[set.id[i]].counters;
   hipEvent_t t1 = timing_mark(c, s);
   if ((rc = cached_normals(c, begin, s)) != AF_OK) return rc;
+  toolset_tools(c, set, host);
   hipEvent_t t2 = timing_mark(c, s);
   score_masks(c, set, host, c->n_points, s, false);
   hipEvent_t t3 = timing_mark(c, s);
@@ -1426,8 +1438,9 @@ int ctx_score_stream(af_ctx *c, const int32_t *tool_ids, int32_t n_tools, void *
   if (!c) return AF_EINVAL;
   ToolSet set;
   ToolDev host[kMultiTools];
-  const int rc = make_toolset(c, tool_ids, n_tools, set, host);
+  const int rc = make_toolset(c, tool_ids, n_tools, set);
   if (rc != AF_OK) return rc;
+  toolset_tools(c, set, host);
   if (n_tools == 1)   // one tool: the single-tool kernel (same results)
     launch_score(c->p, c->pts, host[0], c->grid, c->cfg.max_points, c->score_variant, c->work,
                  (hipStream_t)stream, true);
@@ -1452,8 +1465,9 @@ static int graph_record(af_ctx *c, hipStream_t s) {
   ToolDev host[kMultiTools];
   // (a windowed frame scores its tools one after the other: they share the
   // mask buffers)
-  int rc = make_toolset(c, c->g_ids, c->g_n, set, host, !c->win_on);
+  int rc = make_toolset(c, c->g_ids, c->g_n, set, !c->win_on);
   if (rc != AF_OK) return rc;
+  toolset_tools(c, set, host);
   if (c->win_on && (rc = window_tools_ok(c, c->g_ids, c->g_n)) != AF_OK) return rc;
   if (c->win_on)   // labels of points no graph scored yet read "never evaluated"
     for (int32_t i = 0; i < c->g_n; ++i) {
@@ -1531,8 +1545,7 @@ static int graph_prepare(af_ctx *c, const float lo[3], const float hi[3], int64_
   if (c->win_on && !score)
     return fail(c, AF_EINVAL, "a windowed context scores inside its recorded frame");
   ToolSet set;
-  ToolDev host[kMultiTools];
-  if ((rc = make_toolset(c, tool_ids, n_tools, set, host, !c->win_on)) != AF_OK) return rc;
+  if ((rc = make_toolset(c, tool_ids, n_tools, set, !c->win_on)) != AF_OK) return rc;
   if (c->win_on && (rc = window_tools_ok(c, tool_ids, n_tools)) != AF_OK) return rc;
   hipStream_t s = (hipStream_t)stream;
   HIP_TRY(c, hipStreamSynchronize(s));

@@ -1,0 +1,62 @@
+"""GPU tests of a memory budget that makes an allocation take the room of the
+tools' chunk tables in the middle of a call.  Wherever in the call that
+happens, labels, first free orientations and statistics are those of a context
+without a budget (whole numbers, equal)."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+IDS = [0, 1]
+
+
+def load(synth_mod, budget):
+    from paper_2608_06412_amd import Context, default_config
+    w = synth_mod.tiny()
+    ctx = Context(default_config(w.voxel, w.trunc, r_c=w.r_c, max_blocks=1 << 13, max_points=1 << 14,
+                                 max_orientations=256, max_tools=2, hbm_budget=budget))
+    for i in IDS:
+        ctx.set_tool_kernels(i, synth_mod.cylinder_tool(0.06 - 0.01 * i, 0.3, 1.0),
+                             synth_mod.orientations(synth_mod.fibonacci_directions(128 + 2 * i), 1))
+    return w, ctx
+
+
+def mapped(synth_mod, budget):
+    import torch
+    w, ctx = load(synth_mod, budget)
+    for f in w.frames(4):
+        ctx.integrate_frame(torch.from_numpy(f.xyz).cuda(), f.origin, f.frame_id)
+    return ctx
+
+
+def results(ctx, ids):
+    out = []
+    for i in ids:
+        lab = ctx.read_labels(i)
+        out.append((lab["label"].tolist(), lab["first_free"].tolist(), ctx.score_stats(i)))
+    return out
+
+
+@pytest.mark.parametrize("ids", [[0], [0, 1], [1, 0]])
+def test_dropped_inside_score_tools(synth_mod, ids):
+    ctx = mapped(synth_mod, 0)
+    before = ctx.device_bytes()
+    ctx.score_tools(ids)
+    want, end = results(ctx, ids), ctx.device_bytes()
+    assert 1 in want[0][0] and 2 in want[0][0]
+    ctx = mapped(synth_mod, end - 1)     # the call's last allocation takes the tables' room
+    assert ctx.device_bytes() == before
+    ctx.score_tools(ids)
+    tables = end - ctx.device_bytes()
+    assert tables > 1 << 20
+    assert results(ctx, ids) == want
+    # ... and the others down to the first that still leaves the call enough
+    for budget in np.linspace(max(before, end - tables), end - 1, 7).astype(np.int64)[:-1]:
+        ctx = mapped(synth_mod, int(budget))
+        print("budget", budget, "of", end, flush=True)
+        ctx.score_tools(ids)
+        assert ctx.device_bytes() == end - tables
+        assert results(ctx, ids) == want
+        ctx.score_points(ids[-1])        # and the next calls
+        ctx.score_tools(ids)
+        assert results(ctx, ids) == want
