@@ -237,9 +237,6 @@ int32_t grid_margin_need(const af_ctx *c) {
   return need;
 }
 
-// Grow the brick grid so that it covers block box [lo, hi] with the margin
-// above; new grids are filled with "unknown" (the caller rebuilds them from
-// every block) and every tool's grid-relative table is recomputed.
 // Whether the grid covers the block box with the margin every tool needs.
 static bool grid_covers(const af_ctx *c) {
   if (!c->have_bbox) return true;
@@ -251,6 +248,17 @@ static bool grid_covers(const af_ctx *c) {
   return inside;
 }
 
+static void grid_free(af_ctx *c, const GridDev &g, int64_t bricks) {
+  dev_free(c, g.pred, sizeof(uint32_t) * 32 * bricks);
+  dev_free(c, g.surf, sizeof(uint32_t) * 16 * bricks);
+  dev_free(c, g.occ_any, sizeof(uint32_t) * ((bricks + 31) / 32));
+  dev_free(c, g.occ4, bricks);
+  dev_free(c, g.occ1, sizeof(uint32_t) * 16 * bricks);
+}
+
+// Grow the brick grid so that it covers block box [lo, hi] with the margin
+// above; new grids are filled with "unknown" (the caller rebuilds them from
+// every block) and every tool's grid-relative table is recomputed.
 int ensure_grid(af_ctx *c, hipStream_t s, bool &rebuilt, bool force = false) {
   rebuilt = false;
   const int32_t need = grid_margin_need(c);
@@ -298,18 +306,22 @@ int ensure_grid(af_ctx *c, hipStream_t s, bool &rebuilt, bool force = false) {
   }
   if (c->grid_bricks > 0) {
     HIP_TRY(c, hipStreamSynchronize(s));
-    dev_free(c, g.pred, sizeof(uint32_t) * 32 * c->grid_bricks);
-    dev_free(c, g.surf, sizeof(uint32_t) * 16 * c->grid_bricks);
-    dev_free(c, g.occ_any, sizeof(uint32_t) * ((c->grid_bricks + 31) / 32));
-    dev_free(c, g.occ4, c->grid_bricks);
-    dev_free(c, g.occ1, sizeof(uint32_t) * 16 * c->grid_bricks);
+    grid_free(c, g, c->grid_bricks);
     c->grid_bricks = 0;
+    memset(&g, 0, sizeof(g));
   }
-  ALLOC(c, ng.pred, nb * 32);
-  ALLOC(c, ng.surf, nb * 16);
-  ALLOC(c, ng.occ_any, (nb + 31) / 32);
-  ALLOC(c, ng.occ4, nb);
-  ALLOC(c, ng.occ1, nb * 16);
+  auto planes = [&]() -> int {
+    ALLOC(c, ng.pred, nb * 32);
+    ALLOC(c, ng.surf, nb * 16);
+    ALLOC(c, ng.occ_any, (nb + 31) / 32);
+    ALLOC(c, ng.occ4, nb);
+    ALLOC(c, ng.occ1, nb * 16);
+    return AF_OK;
+  };
+  if (const int rc = planes(); rc != AF_OK) {   // (the planes made so far would keep their room)
+    grid_free(c, ng, nb);
+    return rc;
+  }
   c->grid = ng;
   c->grid_margin = need;
   c->grid_bricks = nb;
