@@ -1057,8 +1057,9 @@ int af_integrate_frame(af_ctx *c, const float *xyz, int64_t n, const float origi
   // The grid has to cover the new blocks before the fold writes their bricks,
   // so the host waits for the counters here.  What does not need the grid is
   // queued before it waits, so the GPU does not (some 20 us a frame).  With a
-  // memory budget the frame stops here when the grid cannot grow, with nothing
-  // of it marked yet.
+  // memory budget the frame stops here when the grid cannot grow: its blocks
+  // stay, for their ids are given out, nothing else of it does, and its frame
+  // id is free for another try.
   const bool ahead = c->cfg.hbm_budget == 0;
   const int64_t touched = std::min<int64_t>(c->cfg.max_blocks, n * (kMaxSpan + kMaxBand));
   hipEvent_t t1{};
@@ -1085,15 +1086,21 @@ int af_integrate_frame(af_ctx *c, const float *xyz, int64_t n, const float origi
     c->have_bbox = true;
   }
   bool rebuilt = false;
-  if ((rc = ensure_grid(c, s, rebuilt, shift)) != AF_OK) {
-    if (ahead) launch_bins_drop(c->map, c->fs, c->counters, s);
-    return rc;
-  }
-  if (!ahead) front(h.n_new_points);
   // new blocks take evicted ids first
   int64_t nb_after = std::min<int64_t>(
       (int64_t)h.blocks_before + std::max<int64_t>(0, (int64_t)h.n_new_blocks - h.free_before),
       c->cfg.max_blocks);
+  if ((rc = ensure_grid(c, s, rebuilt, shift)) != AF_OK) {
+    if (ahead) {
+      launch_bins_drop(c->map, c->fs, c->counters, s);
+    } else {
+      launch_frame_stop(c->map, c->pts, c->fs, c->counters, s);
+      c->n_blocks = nb_after;
+      c->last_stream = s;
+    }
+    return rc;
+  }
+  if (!ahead) front(h.n_new_points);
   launch_fold(c->fargs, c->p, c->map, c->fs, c->counters, c->grid,
                    std::max<int64_t>(1, std::min<int64_t>(nb_after, n * (kMaxSpan + kMaxBand))), s);
   hipEvent_t t2 = timing_mark(c, s);

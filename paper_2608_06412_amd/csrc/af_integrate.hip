@@ -528,6 +528,16 @@ __device__ inline void write_brick(const Params &p, GridDev g, const int32_t S[k
 // cap (Section 3.6) and the block's brick follow in the same workgroup, so
 // the map sees one plain store per voxel and no atomics.
 
+// The ids that k_assign_blocks gave out become part of the map.
+__device__ inline void commit_blocks(const MapDev &m, const FrameCounters *c) {
+  int64_t add = c->n_new_blocks, at = *m.n_blocks;
+  const int64_t nfree = c->free_before;
+  if (m.n_free) *m.n_free = (int32_t)(add < nfree ? nfree - add : 0);
+  add = add > nfree ? add - nfree : 0;
+  if (at + add > m.max_blocks) add = m.max_blocks - at;
+  *m.n_blocks = (int32_t)(at + add);
+}
+
 // The bins' places: any order will do, so each wave takes room for 64 blocks
 // at once.  (A prefix sum in one workgroup took 15 us on a tree frame, this 4.)
 // The frame's new ids also become part of the map here: nothing between the
@@ -554,14 +564,8 @@ k_bin_place(MapDev m, PointsDev pts, FrameScratch fs, FrameCounters *c) {
     }
   }
   if (blockIdx.x != 0 || threadIdx.x != 0) return;
-  int64_t add = c->n_new_blocks, at = *m.n_blocks;
-  const int64_t nfree = c->free_before;
-  if (m.n_free) *m.n_free = (int32_t)(add < nfree ? nfree - add : 0);
-  add = add > nfree ? add - nfree : 0;
-  if (at + add > m.max_blocks) add = m.max_blocks - at;
-  *m.n_blocks = (int32_t)(at + add);
-  at = *pts.n_points;
-  add = c->n_new_points;
+  commit_blocks(m, c);
+  int64_t at = *pts.n_points, add = c->n_new_points;
   if (at + add > pts.max_points) add = pts.max_points - at;
   *pts.n_points = (int32_t)(at + add);
 }
@@ -579,6 +583,17 @@ k_bin_fill(const FrameArgs *fa, Params p, MapDev m, PointsDev pts, FrameScratch 
     if (id >= 0) fs.bin_list[m.tpos[id] + fs.rank[i * cap + r]] = (int32_t)r;
   }
   if (part == kParts - 1) point_view(r, fa->Q, fa->frame, p, pts, fs);
+}
+
+// A frame that ends after its blocks got their ids: the blocks stay in the map,
+// unknown voxels that they are, and the frame's new point keys leave the hash
+// again.  (They are the last ones that entered it, so every other key is found
+// as before, and the slots they took are free as before.)
+__global__ void __launch_bounds__(kThreads)
+k_frame_stop(MapDev m, PointsDev pts, FrameScratch fs, FrameCounters *c) {
+  for (int i = blockIdx.x * kThreads + threadIdx.x; i < c->n_new_points; i += gridDim.x * kThreads)
+    pts.h.keys[fs.new_kslot[i]] = kEmpty;
+  if (blockIdx.x == 0 && threadIdx.x == 0) commit_blocks(m, c);
 }
 
 // Bins that will not be folded: the next frame's start from nothing again.
@@ -1126,6 +1141,10 @@ void launch_bins(const FrameArgs *fa, int64_t nb, const Params &p, MapDev m, Poi
                      dim3(kThreads), 0, s, m, pts, fs, c);
   if (nb > 0)
     hipLaunchKernelGGL(k_bin_fill, dim3(part_grid(nb)), dim3(kPartThreads), 0, s, fa, p, m, pts, fs);
+}
+
+void launch_frame_stop(MapDev m, PointsDev pts, FrameScratch fs, FrameCounters *c, hipStream_t s) {
+  hipLaunchKernelGGL(k_frame_stop, dim3(256), dim3(kThreads), 0, s, m, pts, fs, c);
 }
 
 void launch_bins_drop(MapDev m, FrameScratch fs, FrameCounters *c, hipStream_t s) {

@@ -420,6 +420,8 @@ void launch_bins(const FrameArgs *fa, int64_t nb, const Params &p, MapDev m, Poi
 void launch_fold(const FrameArgs *fa, const Params &p, MapDev m, FrameScratch fs, FrameCounters *c,
                  GridDev g, int64_t max_touched, hipStream_t s);
 void launch_bins_drop(MapDev m, FrameScratch fs, FrameCounters *c, hipStream_t s);
+// Where a frame ends before its touch: its blocks stay, its point keys go.
+void launch_frame_stop(MapDev m, PointsDev pts, FrameScratch fs, FrameCounters *c, hipStream_t s);
 void launch_touch_band(const FrameArgs *fa, int64_t nb, const Params &p, MapDev m,
                        FrameScratch fs, FrameCounters *c, hipStream_t s);
 void launch_points_append(int64_t n_new, MapDev m, PointsDev pts, FrameScratch fs,
