@@ -205,8 +205,10 @@ int af_set_tool_table(af_ctx *ctx, int32_t tool_id, const af_kernel_table *table
  * proportional rescaling of S).  Returns that are non-finite, out of range
  * (|x| >= 2^28 units) or at the sensor position are dropped and counted.
  * `frame_id` must increase strictly (AF_EINVAL otherwise).  The call
- * synchronises `stream` once, after block allocation.  AF_EOVERFLOW when the
- * block or point capacity is exceeded. */
+ * waits once for the block allocation.  AF_EOVERFLOW when the block or point
+ * capacity is exceeded.  AF_ENOMEM when the brick grid cannot grow round the
+ * frame's blocks: the frame is then not integrated (its blocks exist, with
+ * every voxel unknown), and its id may be used again. */
 int af_integrate_frame(af_ctx *ctx, const float *xyz, int64_t n,
                        const float origin[3], int64_t frame_id, void *stream);
 /* af_integrate_frame for returns in HOST memory: `xyz` (n float32 triples)

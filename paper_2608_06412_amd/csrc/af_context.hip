@@ -237,6 +237,10 @@ int32_t grid_margin_need(const af_ctx *c) {
   return need;
 }
 
+// Every block.
+const int3 kAllLo = make_int3(-(1 << 30), -(1 << 30), -(1 << 30));
+const int3 kAllHi = make_int3(1 << 30, 1 << 30, 1 << 30);
+
 // Whether the grid covers the block box with the margin every tool needs.
 static bool grid_covers(const af_ctx *c) {
   if (!c->have_bbox) return true;
@@ -1015,8 +1019,7 @@ int af_integrate_frame(af_ctx *c, const float *xyz, int64_t n, const float origi
   int rc;
   // Section 3.3: the window follows the sensor (see af_set_window)
   bool shift = false, thaw = false;
-  int3 wlo = make_int3(-(1 << 30), -(1 << 30), -(1 << 30));
-  int3 whi = make_int3(1 << 30, 1 << 30, 1 << 30);
+  int3 wlo = kAllLo, whi = kAllHi;
   if (c->win_on) {
     const int32_t qv[3] = {Q.x >> 8, Q.y >> 8, Q.z >> 8};
     shift = window_shift_due(c, Q);
@@ -1050,17 +1053,31 @@ int af_integrate_frame(af_ctx *c, const float *xyz, int64_t n, const float origi
   }
   launch_frame_prep(xyz, c->fargs, {n, Q, frame, wlo, whi}, n, c->p, c->map, c->pts, c->fs, c->counters, s);
   if (thaw) launch_window_thaw(c->map, c->pts, c->fs, c->counters, c->n_points, wlo, whi, s);
-  launch_assign_blocks(c->map, c->fs, c->counters, c->fargs, s);
+  // What does not need the grid is queued before the host's wait below: on the
+  // ground that the grid, as it is, covers the frame's blocks too.  A new block
+  // outside it holds the frame (FrameCounters::held); it is then queued again
+  // after the wait, once the grid has grown.  So nothing of a frame is in the
+  // map, its blocks apart, before it is sure that the frame can end.
+  const bool ahead = !shift && grid_covers(c);
+  int3 glo = kAllLo, ghi = kAllHi;
+  if (ahead) {
+    const int32_t need = grid_margin_need(c);
+    const GridDev &g = c->grid;
+    const bool any = c->grid_bricks > 0;
+    glo = any ? make_int3(g.g0[0] + need, g.g0[1] + need, g.g0[2] + need) : make_int3(0, 0, 0);
+    ghi = any ? make_int3(g.g0[0] + g.gd[0] - 1 - need, g.g0[1] + g.gd[1] - 1 - need,
+                          g.g0[2] + g.gd[2] - 1 - need)
+              : make_int3(-1, -1, -1);
+  }
+  launch_assign_blocks(c->map, c->fs, c->counters, c->fargs, glo, ghi, s);
   if (thaw) launch_window_link(c->map, c->pts, c->n_points, wlo, whi, s);
   HIP_TRY(c, hipMemcpyAsync(c->counters_host, c->counters, offsetof(FrameCounters, fold),
                             hipMemcpyDeviceToHost, s));
   // The grid has to cover the new blocks before the fold writes their bricks,
-  // so the host waits for the counters here.  What does not need the grid is
-  // queued before it waits, so the GPU does not (some 20 us a frame).  With a
-  // memory budget the frame stops here when the grid cannot grow: its blocks
-  // stay, for their ids are given out, nothing else of it does, and its frame
-  // id is free for another try.
-  const bool ahead = c->cfg.hbm_budget == 0;
+  // so the host waits for the counters here, and the GPU has the queued part
+  // meanwhile (some 20 us a frame).  Where the grid cannot grow the frame stops:
+  // its blocks stay, for their ids are given out, nothing else of it does, and
+  // its frame id is free for another try.
   const int64_t touched = std::min<int64_t>(c->cfg.max_blocks, n * (kMaxSpan + kMaxBand));
   hipEvent_t t1{};
   auto front = [&](int64_t new_points) {
@@ -1091,16 +1108,13 @@ int af_integrate_frame(af_ctx *c, const float *xyz, int64_t n, const float origi
       (int64_t)h.blocks_before + std::max<int64_t>(0, (int64_t)h.n_new_blocks - h.free_before),
       c->cfg.max_blocks);
   if ((rc = ensure_grid(c, s, rebuilt, shift)) != AF_OK) {
-    if (ahead) {
-      launch_bins_drop(c->map, c->fs, c->counters, s);
-    } else {
-      launch_frame_stop(c->map, c->pts, c->fs, c->counters, s);
-      c->n_blocks = nb_after;
-      c->last_stream = s;
-    }
+    launch_frame_stop(c->map, c->pts, c->fs, c->counters, s);   // (held, or not queued yet)
+    c->n_blocks = nb_after;
+    c->last_stream = s;
     return rc;
   }
-  if (!ahead) front(h.n_new_points);
+  if (h.held) launch_zero_words(&c->counters->held, sizeof(int32_t), s);
+  if (!ahead || h.held) front(h.n_new_points);
   launch_fold(c->fargs, c->p, c->map, c->fs, c->counters, c->grid,
                    std::max<int64_t>(1, std::min<int64_t>(nb_after, n * (kMaxSpan + kMaxBand))), s);
   hipEvent_t t2 = timing_mark(c, s);
@@ -1510,7 +1524,7 @@ static int graph_record(af_ctx *c, hipStream_t s) {
   FrameArgs given{};   // set before each replay
   given.n = -1;
   launch_frame_prep(c->slot_xyz, c->fargs, given, cap, c->p, c->map, c->pts, c->fs, c->counters, cs);
-  launch_assign_blocks(c->map, c->fs, c->counters, c->fargs, cs);
+  launch_assign_blocks(c->map, c->fs, c->counters, c->fargs, kAllLo, kAllHi, cs);
   launch_touch_band(c->fargs, cap, c->p, c->map, c->fs, c->counters, cs);
   launch_points_append(cap, c->map, c->pts, c->fs, c->counters, c->fargs, cs);
   const int64_t touched = std::min<int64_t>(c->cfg.max_blocks, cap * (kMaxSpan + kMaxBand));
@@ -1639,8 +1653,7 @@ int af_graph_frame(af_ctx *c, const float *xyz, int64_t n, const float origin[3]
   }
   if (n > 0 && xyz != c->slot_xyz)
     HIP_TRY(c, hipMemcpyAsync(c->slot_xyz, xyz, sizeof(float) * 3 * n, hipMemcpyDefault, s));
-  int3 wlo = make_int3(-(1 << 30), -(1 << 30), -(1 << 30));
-  int3 whi = make_int3(1 << 30, 1 << 30, 1 << 30);
+  int3 wlo = kAllLo, whi = kAllHi;
   if (c->win_on) {
     if (!c->gexec || window_shift_due(c, Q)) {
       // the frame that places or moves the window: evictions, block

@@ -200,7 +200,7 @@ __global__ void k_reset_counters(FrameCounters *c, MapDev m, PointsDev pts, Fram
   c->n_valid = c->n_dropped = c->pairs_applied = c->pairs_excluded = 0;
   c->band_marks = c->voxels_folded = 0;
   c->n_new_blocks = c->n_touched = c->n_new_points = c->status = 0;
-  c->n_changed = c->n_binned = 0;
+  c->n_changed = c->n_binned = c->held = 0;
   for (int i = 0; i < 3; ++i) {
     c->bmin[i] = 0x7fffffff;
     c->bmax[i] = -0x7fffffff - 1;
@@ -212,7 +212,7 @@ __global__ void k_reset_counters(FrameCounters *c, MapDev m, PointsDev pts, Fram
 
 // One workgroup per new block: assign its id and clear its voxels.
 __global__ void __launch_bounds__(kThreads)
-k_assign_blocks(MapDev m, FrameScratch fs, FrameCounters *c, const FrameArgs *fa) {
+k_assign_blocks(MapDev m, FrameScratch fs, FrameCounters *c, const FrameArgs *fa, int3 glo, int3 ghi) {
   const int32_t frame = fa->frame;
   int n_new = c->n_new_blocks;
   int64_t base = *m.n_blocks;
@@ -239,6 +239,7 @@ k_assign_blocks(MapDev m, FrameScratch fs, FrameCounters *c, const FrameArgs *fa
         atomicMin(&c->bmin[a], b[a]);
         atomicMax(&c->bmax[a], b[a]);
       }
+      if (!in_box(b[0], b[1], b[2], glo, ghi)) atomicOr(&c->held, 1);
     }
     for (int t = threadIdx.x; t < kBlockVox; t += kThreads) {
       m.S[id * kBlockVox + t] = 0;
@@ -290,7 +291,7 @@ k_touch_band(const FrameArgs *fa, Params p, MapDev m, FrameScratch fs, FrameCoun
   const int32_t frame = fa->frame;
   const int part = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const int64_t r = (int64_t)blockIdx.x * 64 + lane_id();
-  if ((int64_t)blockIdx.x * 64 >= n) return;
+  if (((int64_t)blockIdx.x * 64 >= n) | (c->held != 0)) return;
   __shared__ int32_t s_new[64 * (kMaxSpan + kMaxBand)];   // blocks this workgroup touched first
   __shared__ int s_count[3];                              // those, their place in the list, marks
   __shared__ int s_group[kParts][2][64];                  // see grouped_add
@@ -351,7 +352,7 @@ k_sort_new_tiles(FrameScratch fs, const FrameCounters *c) {
   __shared__ int64_t v[kThreads];
   const int m = c->n_new_points;
   const int base = blockIdx.x * kThreads;
-  if (base >= m) return;
+  if ((base >= m) | (c->held != 0)) return;
   const int t = threadIdx.x;
   v[t] = base + t < m ? fs.new_keys[base + t] : (int64_t)0x7fffffffffffffffLL;
   __syncthreads();
@@ -381,7 +382,7 @@ k_points_append(MapDev m, PointsDev pts, FrameScratch fs, FrameCounters *c, cons
   const int mcount = c->n_new_points;
   const int lane = lane_id(), wave = (int)(threadIdx.x >> 6);
   const int i = blockIdx.x * 64 + lane;
-  if ((int)(blockIdx.x * 64) >= mcount) return;
+  if (((int)(blockIdx.x * 64) >= mcount) | (c->held != 0)) return;
   const int64_t key = fs.new_keys[i < mcount ? i : 0];
   int part = 0;
   for (int base = wave * kThreads; base < mcount; base += kAppendWaves * kThreads) {
@@ -544,7 +545,7 @@ __device__ inline void commit_blocks(const MapDev &m, const FrameCounters *c) {
 // assignment and this kernel reads the counts as they were, nothing after.
 __global__ void __launch_bounds__(kThreads)
 k_bin_place(MapDev m, PointsDev pts, FrameScratch fs, FrameCounters *c) {
-  const int nt = c->n_touched;
+  const int nt = c->n_touched;   // (0 in a frame that is held)
   const int lane = lane_id();
   for (int j0 = (blockIdx.x * kThreads + threadIdx.x) & ~63; j0 < nt; j0 += gridDim.x * kThreads) {
     const int j = j0 + lane;
@@ -563,7 +564,7 @@ k_bin_place(MapDev m, PointsDev pts, FrameScratch fs, FrameCounters *c) {
       m.tpos[id] = base;
     }
   }
-  if (blockIdx.x != 0 || threadIdx.x != 0) return;
+  if (blockIdx.x != 0 || threadIdx.x != 0 || c->held) return;
   commit_blocks(m, c);
   int64_t at = *pts.n_points, add = c->n_new_points;
   if (at + add > pts.max_points) add = pts.max_points - at;
@@ -572,11 +573,12 @@ k_bin_place(MapDev m, PointsDev pts, FrameScratch fs, FrameCounters *c) {
 
 // Each return into the bins of its blocks, and its viewpoint to its point.
 __global__ void __launch_bounds__(kPartThreads)
-k_bin_fill(const FrameArgs *fa, Params p, MapDev m, PointsDev pts, FrameScratch fs) {
+k_bin_fill(const FrameArgs *fa, Params p, MapDev m, PointsDev pts, FrameScratch fs,
+           const FrameCounters *c) {
   const int64_t n = fa->n, cap = fs.cap;
   const int part = (int)(threadIdx.x >> 6);
   const int64_t r = (int64_t)blockIdx.x * 64 + lane_id();
-  if (r >= n) return;
+  if ((r >= n) | (c->held != 0)) return;
   const int side = span_side(p.R);
   for (int i = part; i < side * side * side; i += kParts) {
     const int32_t id = fs.span[i * cap + r];
@@ -594,12 +596,6 @@ k_frame_stop(MapDev m, PointsDev pts, FrameScratch fs, FrameCounters *c) {
   for (int i = blockIdx.x * kThreads + threadIdx.x; i < c->n_new_points; i += gridDim.x * kThreads)
     pts.h.keys[fs.new_kslot[i]] = kEmpty;
   if (blockIdx.x == 0 && threadIdx.x == 0) commit_blocks(m, c);
-}
-
-// Bins that will not be folded: the next frame's start from nothing again.
-__global__ void __launch_bounds__(kThreads) k_bin_drop(MapDev m, FrameScratch fs, FrameCounters *c) {
-  for (int i = blockIdx.x * kThreads + threadIdx.x; i < c->n_touched; i += gridDim.x * kThreads)
-    m.tpos[fs.touched[i]] = 0;
 }
 
 // A block's returns are dealt to its workgroup's eight waves; a wave takes up
@@ -1130,9 +1126,9 @@ void launch_frame_prep(const float *xyz, FrameArgs *fa, const FrameArgs &fa_new,
                        pts, fs, c);
 }
 
-void launch_assign_blocks(MapDev m, FrameScratch fs, FrameCounters *c, const FrameArgs *fa,
-                          hipStream_t s) {
-  hipLaunchKernelGGL(k_assign_blocks, dim3(4096), dim3(kThreads), 0, s, m, fs, c, fa);
+void launch_assign_blocks(MapDev m, FrameScratch fs, FrameCounters *c, const FrameArgs *fa, int3 glo,
+                          int3 ghi, hipStream_t s) {
+  hipLaunchKernelGGL(k_assign_blocks, dim3(4096), dim3(kThreads), 0, s, m, fs, c, fa, glo, ghi);
 }
 
 void launch_bins(const FrameArgs *fa, int64_t nb, const Params &p, MapDev m, PointsDev pts,
@@ -1140,15 +1136,11 @@ void launch_bins(const FrameArgs *fa, int64_t nb, const Params &p, MapDev m, Poi
   hipLaunchKernelGGL(k_bin_place, dim3((unsigned)std::min<int64_t>(256, grid_for(max_touched))),
                      dim3(kThreads), 0, s, m, pts, fs, c);
   if (nb > 0)
-    hipLaunchKernelGGL(k_bin_fill, dim3(part_grid(nb)), dim3(kPartThreads), 0, s, fa, p, m, pts, fs);
+    hipLaunchKernelGGL(k_bin_fill, dim3(part_grid(nb)), dim3(kPartThreads), 0, s, fa, p, m, pts, fs, c);
 }
 
 void launch_frame_stop(MapDev m, PointsDev pts, FrameScratch fs, FrameCounters *c, hipStream_t s) {
   hipLaunchKernelGGL(k_frame_stop, dim3(256), dim3(kThreads), 0, s, m, pts, fs, c);
-}
-
-void launch_bins_drop(MapDev m, FrameScratch fs, FrameCounters *c, hipStream_t s) {
-  hipLaunchKernelGGL(k_bin_drop, dim3(256), dim3(kThreads), 0, s, m, fs, c);
 }
 
 void launch_fold(const FrameArgs *fa, const Params &p, MapDev m, FrameScratch fs, FrameCounters *c,

@@ -70,6 +70,8 @@ struct FrameCounters {
   unsigned long long band_marks, voxels_folded;
   int32_t n_new_blocks, n_touched, n_new_points, status;
   int32_t n_binned;    // (return, block) pairs given room in the bins
+  int32_t held;        // a new block lies outside the box the frame was queued for: what is
+                       // queued after the ids leaves the frame as it is (launch_assign_blocks)
   int32_t n_changed;   // voxels that received a contribution (listed when fs.changed is set)
   int32_t bmin[3], bmax[3];
   int32_t blocks_before, points_before;
@@ -411,15 +413,16 @@ void launch_zero_words(void *p, int64_t bytes, hipStream_t s);   // a fill kerne
 void launch_frame_prep(const float *xyz, FrameArgs *fa, const FrameArgs &fa_new, int64_t nb,
                        const Params &p, MapDev m, PointsDev pts, FrameScratch fs, FrameCounters *c,
                        hipStream_t s);
-void launch_assign_blocks(MapDev m, FrameScratch fs, FrameCounters *c, const FrameArgs *fa,
-                          hipStream_t s);
+// glo, ghi: the block box that what is queued next may take the frame in (held
+// if one of its new blocks lies outside)
+void launch_assign_blocks(MapDev m, FrameScratch fs, FrameCounters *c, const FrameArgs *fa, int3 glo,
+                          int3 ghi, hipStream_t s);
 // Viewpoints and bins; the frame's new ids become part of the map.  Then the
-// fold and the bricks, or, where a frame ends before its fold, the bins dropped.
+// fold and the bricks.
 void launch_bins(const FrameArgs *fa, int64_t nb, const Params &p, MapDev m, PointsDev pts,
                  FrameScratch fs, FrameCounters *c, int64_t max_touched, hipStream_t s);
 void launch_fold(const FrameArgs *fa, const Params &p, MapDev m, FrameScratch fs, FrameCounters *c,
                  GridDev g, int64_t max_touched, hipStream_t s);
-void launch_bins_drop(MapDev m, FrameScratch fs, FrameCounters *c, hipStream_t s);
 // Where a frame ends before its touch: its blocks stay, its point keys go.
 void launch_frame_stop(MapDev m, PointsDev pts, FrameScratch fs, FrameCounters *c, hipStream_t s);
 void launch_touch_band(const FrameArgs *fa, int64_t nb, const Params &p, MapDev m,

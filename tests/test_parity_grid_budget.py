@@ -55,10 +55,10 @@ def test_failed_growth_gives_its_planes_back(synth_mod):
     assert scores(ctx) == want
 
 
-def far_frame(synth_mod, w, i):
-    """Frame i with returns 2 m away on every side, three times each."""
+def far_frame(synth_mod, w, i, far=2.0):
+    """Frame i with returns `far` metres away on every side, three times each."""
     f = w.frames(i + 1)[i]
-    d = np.concatenate([np.eye(3), -np.eye(3)]).astype(np.float32) * 2
+    d = np.concatenate([np.eye(3), -np.eye(3)]).astype(np.float32) * np.float32(far)
     return dataclasses.replace(f, xyz=np.concatenate([f.xyz, d, d, d]).astype(np.float32))
 
 
@@ -129,3 +129,21 @@ def test_frames_go_on_after_a_refused_one(synth_mod, again, window):
         c.score_points(0)
     assert scores(ctx) == scores(ref)
     assert ref.score_stats(0)["n_confident"] > 100
+
+
+def test_refused_frame_leaves_the_map_as_it_was(synth_mod):
+    """Without a budget: no grid covers returns 900 m away."""
+    from paper_2608_06412_amd import AFError
+    w, ctx = context(synth_mod, 0)
+    _, ref = context(synth_mod, 0)
+    f = w.frames(3)
+    for c in (ctx, ref):
+        integrate(c, f[0])
+        integrate(c, f[1])
+    for _ in range(3):
+        with pytest.raises(AFError) as e:
+            integrate(ctx, far_frame(synth_mod, w, 2, 900.0))
+        assert e.value.code == ENOMEM
+        same_map(ctx, ref)
+    with pytest.raises(AFError):
+        integrate(ctx, f[1])      # (ids increase)
