@@ -171,7 +171,16 @@ bool drop_chunks(af_ctx *c) {
 
 int dev_alloc(af_ctx *c, void **p, int64_t bytes) {
   int rc = dev_alloc_once(c, p, bytes);
-  if (rc != AF_OK && drop_chunks(c)) rc = dev_alloc_once(c, p, bytes);
+  if (rc == AF_OK) return rc;
+  // (never rebuilt before their tool is loaded again: not dropped in vain)
+  int64_t room = 0;
+  for (const ToolDev &t : c->tools)
+    if (t.pent) room += chunk_bytes(t) + (int64_t)sizeof(uint4) * t.K;
+  size_t left = 0, total = 0;
+  const bool enough = c->cfg.hbm_budget > 0 && c->bytes + bytes > c->cfg.hbm_budget
+                          ? c->bytes - room + bytes <= c->cfg.hbm_budget
+                          : hipMemGetInfo(&left, &total) == hipSuccess && (int64_t)left + room >= bytes;
+  if (enough && drop_chunks(c)) rc = dev_alloc_once(c, p, bytes);
   return rc;
 }
 

@@ -60,3 +60,25 @@ def test_dropped_inside_score_tools(synth_mod, ids):
         ctx.score_points(ids[-1])        # and the next calls
         ctx.score_tools(ids)
         assert results(ctx, ids) == want
+
+
+def test_kept_when_their_room_is_not_enough(synth_mod):
+    """A call that does not fit even in the tables' room is refused and leaves
+    them; one that does takes it."""
+    from paper_2608_06412_amd import AFError
+    ctx = mapped(synth_mod, 0)
+    ctx.score_points(0)
+    held, want = ctx.device_bytes(), results(ctx, [0])
+    ctx = mapped(synth_mod, held)
+    ctx.score_points(0)
+    for n in (1 << 21, 1 << 22):
+        with pytest.raises(AFError) as e:
+            ctx.integrate_frame(np.zeros((n, 3), np.float32), np.zeros(3, np.float32), 100)
+        assert e.value.code == -2
+        assert ctx.device_bytes() == held
+    ctx.score_points(0)
+    assert results(ctx, [0]) == want
+    ctx.integrate_frame(np.zeros((1500, 3), np.float32), np.zeros(3, np.float32), 100)
+    assert ctx.device_bytes() < held
+    ctx.score_points(0)
+    assert results(ctx, [0]) == want
