@@ -47,6 +47,7 @@ struct af_ctx {
   int64_t slot_cap;
   bool graph_dirty;             // recorded frames ran since the host mirrors were refreshed
   bool graph_stale;             // a buffer the graph holds was reallocated
+  bool graph_tables;            // chunk tables it holds were dropped
   bool sticky_reset;            // the host has read the sticky status: the next frame clears it
   // what the graph was prepared with (a windowed context records it again
   // after every shift of the window)
@@ -165,7 +166,7 @@ bool drop_chunks(af_ctx *c) {
     dev_free(c, pmeta, sizeof(uint4) * t.K);
     any = true;
   }
-  if (any) c->graph_stale = true;
+  if (any) c->graph_tables = true;
   return any;
 }
 
@@ -1570,7 +1571,7 @@ static int graph_record(af_ctx *c, hipStream_t s) {
     return fail(c, AF_EDEVICE, "frame graph capture: %s", hipGetErrorString(e1));
   c->graph = g;
   HIP_TRY(c, hipGraphInstantiate(&c->gexec, c->graph, nullptr, nullptr, 0));
-  c->graph_stale = false;
+  c->graph_stale = c->graph_tables = false;
   c->last_stream = s;
   return hip_check(c, "graph record");
 }
@@ -1663,6 +1664,11 @@ int af_graph_frame(af_ctx *c, const float *xyz, int64_t n, const float origin[3]
   if (n > 0 && xyz != c->slot_xyz)
     HIP_TRY(c, hipMemcpyAsync(c->slot_xyz, xyz, sizeof(float) * 3 * n, hipMemcpyDefault, s));
   int3 wlo = kAllLo, whi = kAllHi;
+  if (!c->win_on && c->graph_tables) {   // (the tables it reads are gone, nothing else)
+    int rc;
+    if (c->graph_dirty && (rc = graph_settle(c)) != AF_OK) return rc;
+    if ((rc = graph_record(c, s)) != AF_OK) return rc;
+  }
   if (c->win_on) {
     if (!c->gexec || window_shift_due(c, Q)) {
       // the frame that places or moves the window: evictions, block
@@ -1675,7 +1681,7 @@ int af_graph_frame(af_ctx *c, const float *xyz, int64_t n, const float origin[3]
       if ((rc = score_window(c, c->g_ids, c->g_n, s)) != AF_OK) return rc;
       return graph_record(c, s);
     }
-    if (c->graph_stale) {   // (a windowed context records the frame again)
+    if (c->graph_stale || c->graph_tables) {   // (a windowed context records the frame again)
       int rc;
       if (c->graph_dirty && (rc = graph_settle(c)) != AF_OK) return rc;
       if ((rc = graph_record(c, s)) != AF_OK) return rc;
