@@ -135,7 +135,10 @@ int dev_alloc_once(af_ctx *c, void **p, int64_t bytes) {
     return fail(c, AF_ENOMEM, "HBM budget of %lld bytes exceeded (need %lld more)",
                 (long long)c->cfg.hbm_budget, (long long)bytes);
   hipError_t e = hipMalloc(p, (size_t)bytes);
-  if (e != hipSuccess) return fail(c, AF_ENOMEM, "hipMalloc(%lld): %s", (long long)bytes, hipGetErrorString(e));
+  if (e != hipSuccess) {
+    (void)hipGetLastError();   // (the caller may go on without: not the next launch's error)
+    return fail(c, AF_ENOMEM, "hipMalloc(%lld): %s", (long long)bytes, hipGetErrorString(e));
+  }
   c->bytes += bytes;
   c->allocs.push_back(*p);
   return AF_OK;

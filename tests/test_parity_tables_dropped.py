@@ -126,3 +126,19 @@ def test_recorded_frames_go_on_after_a_drop(synth_mod, ids):
         eager.integrate_frame(x, f.origin, f.frame_id)
     eager.score_tools(ids)
     assert results(eager, ids) == got[-1]
+
+
+def test_refused_by_the_device_is_no_later_error(synth_mod):
+    """A device allocation that fails is reported by its call, not by the next
+    launch (a context goes on, where it can, without what it did not get)."""
+    import torch
+    from paper_2608_06412_amd import AFError
+    ctx, ref = mapped(synth_mod, 0), mapped(synth_mod, 0)
+    with pytest.raises(AFError) as e:
+        ctx.graph_prepare([-3, -3, -1], [3, 3, 3], 1 << 40, [0])   # 16 TiB of scratch
+    assert e.value.code == -2
+    f = synth_mod.tiny().frames(6)[5]
+    for c in (ctx, ref):
+        c.integrate_frame(torch.from_numpy(f.xyz).cuda(), f.origin, f.frame_id)
+        c.score_tools(IDS)
+    assert results(ctx, IDS) == results(ref, IDS)
