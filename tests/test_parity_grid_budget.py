@@ -51,6 +51,10 @@ def test_failed_growth_gives_its_planes_back(synth_mod):
         held.append(ctx.device_bytes())
     assert held[0] == held[1] == held[2]
     ctx.set_tool_kernels(0, w.tool, w.rot)
+    _, ref = context(synth_mod, 0)
+    integrate(ref, f)
+    ref.set_tool_kernels(0, w.tool, w.rot)
+    assert ctx.device_bytes() == ref.device_bytes()
     ctx.score_points(0)
     assert scores(ctx) == want
 
