@@ -347,10 +347,10 @@ int af_score_tools(af_ctx *ctx, const int32_t *tool_ids, int32_t n_tools, void *
  * plane ("bit") as options, and "chunk" (64 entries a step, the corridor's
  * occupied cells naming the steps to read).  All give identical labels, first free
  * orientations and canonical counts; they differ in speed only.  A new
- * context uses af_score_variant_default(); configurations that need K <= 256
- * fall back to configuration 0 for larger K.  af_tune_score times every
- * configuration `reps` times on the
- * context's current map and tool (HIP events on `stream`), keeps the fastest
+ * context uses af_score_variant_default(); a configuration that a tool or the
+ * grid does not admit (K above its limit, no room for its tables, a grid too
+ * wide for its offsets) is replaced by one that they do.  af_tune_score times
+ * every configuration `reps` times on the context's current map and tool (HIP events on `stream`), keeps the fastest
  * for later af_score_points calls, writes its index to *best and, if
  * ms_per_variant is not NULL, each configuration's mean time (host array of
  * af_score_variant_count() floats).  Synchronises `stream`. */

@@ -1181,7 +1181,7 @@ __device__ inline bool corridor_clear4_sw(const ToolDev &t, const SwGrid &q, con
 // Entries [b, e) of orientation k after its first E: body entries finely,
 // then the corridor -- skipped when its 4^3 cells are clear (CO), finely
 // otherwise.  Canonical lookups stay the table-order count.
-template <int UN, int CO, int B1, int RE = 0, int LZ = 0>
+template <int UN, int CO, int B1, int RE = 0, int LZ = 0, int UC = 0, int UB = 0>
 __device__ inline bool scan_rest_sw(const Params &p, const ToolDev &t, const SwGrid &q,
                                     const SwFrame &f, int k, uint32_t b, uint32_t e, int body,
                                     uint32_t &lookups, uint32_t &cchecks, uint32_t &cclear,
@@ -1191,8 +1191,18 @@ __device__ inline bool scan_rest_sw(const Params &p, const ToolDev &t, const SwG
   if (!CO) return scan_fine_sw<UN, B1, RE, 0, LZ>(p, t, q, f, b, e, body, lookups, sbody, first);
   const uint32_t fb = t.far_begin[k];
   const uint32_t mid = fb > b ? fb : b;
-  if (!scan_fine_sw<UN, B1, RE, B1 ? 1 : 0, LZ>(p, t, q, f, b, mid, body, lookups, sbody, first))
-    return false;
+  if constexpr (UB > 0) {
+    // the body's first chunk alone (most blocked candidates end there), the
+    // rest UB chunks per step
+    const uint32_t c1 = b + 64u < mid ? b + 64u : mid;
+    if (!scan_fine_sw<UN, B1, RE, B1 ? 1 : 0, LZ>(p, t, q, f, b, c1, body, lookups, sbody, first))
+      return false;
+    if (!scan_fine_sw<UB, B1, RE, B1 ? 1 : 0, LZ>(p, t, q, f, c1, mid, body, lookups, sbody))
+      return false;
+  } else {
+    if (!scan_fine_sw<UN, B1, RE, B1 ? 1 : 0, LZ>(p, t, q, f, b, mid, body, lookups, sbody, first))
+      return false;
+  }
   if (mid >= e) return true;
   if (t.c4flag[k] != 0) {
     ++cchecks;
@@ -1202,7 +1212,11 @@ __device__ inline bool scan_rest_sw(const Params &p, const ToolDev &t, const SwG
       return true;
     }
   }
-  return scan_fine_sw<UN, B1, RE, B1 ? 2 : 0, LZ>(p, t, q, f, mid, e, body, lookups, sfar);
+  // the corridor: UC chunks per step (0: UN); a candidate that gets this far
+  // is mostly free and reads its whole corridor, so two chunks in flight
+  // hide one gather latency at little waste
+  return scan_fine_sw<UC ? UC : UN, B1, RE, B1 ? 2 : 0, LZ>(p, t, q, f, mid, e, body, lookups,
+                                                          sfar);
 }
 
 // Candidate-parallel scoring with grid-relative lookups (the configurations
@@ -1439,10 +1453,14 @@ __device__ inline void near_flush(ScoreCounterBlock &sc, NearAcc &a, int lane) {
 
 // One point of the "near" scoring (see k_score_near): label and first free
 // orientation of point i for tool t, whose begin offsets are s_begin.
-template <int UN, int CO, int B1, int PF, int RE, int LZ = 0>
+// LF: s_first holds, for every orientation k, its 64 entries after the arm
+// samples (lane l: entry min(begin[k] + 3 + l, begin[k + 1] - 1)), 4-byte
+// form, so a candidate's first step reads its entries from LDS.
+template <int UN, int CO, int B1, int PF, int RE, int LZ = 0, int UC = 0, int UB = 0, int LF = 0>
 __device__ inline void near_point(const Params &p, const PointsDev &pts, const ToolDev &t,
                                   const GridDev &g, const SwGrid &q, const uint32_t *s_begin,
-                                  int32_t mw, int64_t i, int lane, NearAcc &acc) {
+                                  int32_t mw, int64_t i, int lane, NearAcc &acc,
+                                  const uint32_t *s_first = nullptr) {
   constexpr uint32_t E = 3;   // the arm samples
   constexpr int F = 64 / PF;  // prefix entries per candidate when PF > 1
   static_assert(PF == 1 || PF == 2 || PF == 4 || PF == 8, "PF divides the wave");
@@ -1480,9 +1498,14 @@ __device__ inline void near_point(const Params &p, const PointsDev &pts, const T
       Ent pre{};
       auto first_step = [&](uint64_t o) {
         const int kn = 64 * w + (__ffsll((long long)o) - 1);
-        const uint32_t bn = s_begin[kn] + E, en = s_begin[kn + 1];
-        const uint32_t idx = bn + (uint32_t)lane;
-        return load_entry<RE>(t, idx < en ? idx : en - 1);
+        if constexpr (LF != 0) {
+          static_assert(RE == 1 && PF == 1 && UN == 1, "4-byte entries, one step");
+          return (Ent)s_first[kn * 64 + lane];
+        } else {
+          const uint32_t bn = s_begin[kn] + E, en = s_begin[kn + 1];
+          const uint32_t idx = bn + (uint32_t)lane;
+          return load_entry<RE>(t, idx < en ? idx : en - 1);
+        }
       };
       if (PF == 1 && open) pre = first_step(open);
       while (open && ff < 0) {
@@ -1545,7 +1568,7 @@ __device__ inline void near_point(const Params &p, const PointsDev &pts, const T
             body = __popcll(bm1);
             start = b + nin;
           }
-          if (scan_rest_sw<UN, CO, B1, RE, LZ>(
+          if (scan_rest_sw<UN, CO, B1, RE, LZ, UC, UB>(
                   p, t, q, f, kj, start, e, body, acc.lookups, acc.cchecks, acc.cclear, acc.sbody,
                   acc.sfar, c4, g.occ4, PF == 1 && UN == 1 ? &cur : nullptr)) {
             ff = (int16_t)kj;
@@ -1580,7 +1603,8 @@ __device__ inline void near_point(const Params &p, const PointsDev &pts, const T
 // only the undecided ones continue lane-parallel.  Requires K <= kNearK.
 // Same labels, first free orientations and canonical counts as the plain
 // scan.
-template <int NT, int UN, int FB, int CO, int B1, int DIAG, int PF = 1, int RE = 0>
+template <int NT, int UN, int FB, int CO, int B1, int DIAG, int PF = 1, int RE = 0, int UC = 0,
+          int UB = 0, int LF = 0>
 __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(8)))
 k_score_near(Params p, PointsDev pts, ToolDev t, GridDev g, int64_t n, int32_t mw,
              unsigned *work) {
@@ -1588,8 +1612,19 @@ k_score_near(Params p, PointsDev pts, ToolDev t, GridDev g, int64_t n, int32_t m
   if (n < 0) n = pts.sel ? (int64_t)*pts.n_sel : (int64_t)*pts.n_points;
   constexpr int NW = NT / 64;
   __shared__ uint32_t s_begin[kNearK + 1];
+  // LF: the first 64 entries after the arm samples of every orientation
+  // (K <= kLfK, 64 KiB), read from LDS instead of the table
+  __shared__ uint32_t s_first[LF ? kLfK * 64 : 1];
   const int K = t.K;
   for (int j = threadIdx.x; j <= K; j += NT) s_begin[j] = t.begin[j];
+  if constexpr (LF != 0) {
+    static_assert(NT == 1024, "two workgroups of 68 KiB LDS fill a CU's 160 KiB at 8 waves/SIMD");
+    for (int j = threadIdx.x; j < K * 64; j += NT) {
+      const uint32_t b = t.begin[j >> 6] + 3u, e = t.begin[(j >> 6) + 1];
+      const uint32_t idx = b + (uint32_t)(j & 63);
+      s_first[j] = load_entry<1>(t, idx < e ? idx : e - 1);
+    }
+  }
   __syncthreads();
   const SwGrid q = sw_grid(g);
   const int lane = lane_id();
@@ -1620,7 +1655,8 @@ k_score_near(Params p, PointsDev pts, ToolDev t, GridDev g, int64_t n, int32_t m
         !pts.sel ? i
         : FB > 0 ? (int64_t)__builtin_amdgcn_readlane(selv, (int)(FB - (batch_end - i)))
                  : (int64_t)__builtin_amdgcn_readfirstlane(pts.sel[i]);
-    near_point<UN, CO, B1, PF, RE, 1>(p, pts, t, g, q, s_begin, mw, pi, lane, a);
+    near_point<UN, CO, B1, PF, RE, 1, UC, UB, LF>(p, pts, t, g, q, s_begin, mw, pi, lane, a,
+                                                  s_first);
     if (a.lookups > (1u << 30)) near_flush<DIAG>(sc, a, lane);
     if (FB > 0) {
       if (++i >= batch_end) {
@@ -2312,12 +2348,21 @@ const ScoreVariant kVariants[] = {
     {k_score_near<256, 2, 8, 2, 1, 0, 1, 1>, 256, "near wg256 unroll2 dyn8 coarse4 bit rel", kNearK, 1},
     {k_score_near<512, 1, 8, 2, 1, 0, 1, 1>, 512, "near wg512 unroll1 dyn8 coarse4 bit rel", kNearK, 1},
     {k_score_near<256, 1, 8, 2, 1, 0, 2, 1>, 256, "near wg256 unroll1 dyn8 coarse4 bit prefix2 rel", kNearK, 1},
+    {k_score_near<256, 1, 8, 2, 1, 0, 1, 1, 2>, 256, "near wg256 unroll1 dyn8 coarse4 bit rel corr2", kNearK, 1},
+    {k_score_near<256, 1, 8, 2, 1, 1, 1, 1, 2>, 256, "near wg256 unroll1 dyn8 coarse4 bit rel corr2 diag", kNearK, 1},
+    {k_score_near<256, 1, 8, 2, 1, 0, 1, 1, 0, 2>, 256, "near wg256 unroll1 dyn8 coarse4 bit rel body2", kNearK, 1},
+    {k_score_near<1024, 1, 8, 2, 1, 0, 1, 1, 2, 0, 1>, 1024,
+     "near wg1024 unroll1 dyn8 coarse4 bit rel corr2 lds1", kLfK, 1,
+     "near wg256 unroll1 dyn8 coarse4 bit rel corr2"},
     {k_score_chunk<256, 0>, 256, "chunk wg256", kNearK, 1, nullptr, 1},
     {k_score_chunk<1024, 1>, 1024, "chunk wg1024 lds1", kLfK, 1, "chunk wg256", 1},
-    {k_score_chunk<512, 0>, 512, "chunk wg512", kNearK, 1, nullptr, 1},
-    {k_score_chunk<1024, 0>, 1024, "chunk wg1024", kNearK, 1, nullptr, 1},
 };
-constexpr int kChunkElse = 6;   // where the chunk scan cannot run
+// Where the chunk scan cannot run (no table, or a grid beyond its offsets): the
+// fastest of the others.  (Tree survey of 605,000 points, kernel: 256
+// orientations 1.20 ms, 1.22 in the form without staged entries, 0.88 by
+// chunks; 291, which take its above_k, 1.31, 1.33 and 0.91; 1,024 2.53, 2.61
+// and 1.98.)
+const char *const kChunkElse = "near wg1024 unroll1 dyn8 coarse4 bit rel corr2 lds1";
 constexpr int kNumVariants = (int)(sizeof(kVariants) / sizeof(kVariants[0]));
 
 static int variant_index(const char *name) {
@@ -2571,11 +2616,12 @@ int launch_score_jobs(const ScoreJob *jobs_dev, const ScoreJob *jobs_host, int32
 
 static int effective_variant(int variant, const ToolDev &t, const GridDev *g = nullptr) {
   if (variant < 0 || variant >= kNumVariants) variant = 0;
+  if (kVariants[variant].chunk && (!t.pent || (g && !chunk_grid_ok(*g))))
+    variant = variant_index(kChunkElse);
   if (kVariants[variant].max_k && t.K > kVariants[variant].max_k)
     variant = kVariants[variant].above_k ? variant_index(kVariants[variant].above_k) : 0;
   if (kVariants[variant].max_k && t.K > kVariants[variant].max_k) variant = 0;
   if (kVariants[variant].needs_rel && !t.rent) variant = 0;
-  if (kVariants[variant].chunk && (!t.pent || (g && !chunk_grid_ok(*g)))) variant = kChunkElse;
   return variant;
 }
 
