@@ -265,8 +265,10 @@ __device__ inline PairView pair_view(const PairBase &pb, const double Rv[9], int
   return w;
 }
 
-// No sample's cell: a coordinate that a sample's double cannot reach (the
-// conversion to int stops there at 2^31 - 1 plus the point's).
+// No sample's cell: smooth_sample keeps x above it.  (A point or a sample beyond
+// 2^31 voxels has a coordinate anywhere: the conversion to int stops at the
+// ends, and their sum wraps.  With the values set instead, so that no cell
+// would do, the refinement takes 2.2 ms, not 1.95.)
 constexpr int kNoCell = -0x7fffffff - 1;
 
 // A lane's cell of a pair and its values, kept while the samples stay in their
@@ -298,6 +300,7 @@ __device__ inline float smooth_sample(const FieldView &f, const PairView &w, con
     fr[a] = (float)(gl - fl);
     u[a] = (float)ud;
   }
+  at[0] = at[0] > kNoCell ? at[0] : kNoCell + 1;   // (both are outside every grid)
   if ((at[0] != cell.x[0]) | (at[1] != cell.x[1]) | (at[2] != cell.x[2])) {
     for (int a = 0; a < 3; ++a) cell.x[a] = at[a];
     cell_values(f, at[0], at[1], at[2], cell.t);
