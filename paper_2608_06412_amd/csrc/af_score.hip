@@ -557,10 +557,11 @@ __device__ inline uint32_t ent_code(const SwGrid &q, const SwFrame &f, uint32_t 
 
 // Candidate masks (Section 3.4 "Approach directions"): one lane per point,
 // its normal and viewpoint vectors in registers (float, with a test in double
-// on the exact integers where float does not decide).  For every candidate direction the lane also reads the
-// direction's three arm samples (Section 3.4 "Arm path checking"; they depend
-// on the approach direction only, so orientations that share it share the
-// result) and records which one hits first, as two bit planes per mask word.
+// on the exact integers where float does not decide).  For every candidate
+// direction the lane also reads the direction's three arm samples (Section 3.4
+// "Arm path checking"; they depend on the approach direction only, so
+// orientations that share it share the result) and records which one hits
+// first, as two bit planes per mask word.
 // An orientation that shares its predecessor's approach direction takes its
 // candidate bit and arm-sample result, so only heads (orientations with a
 // direction of their own) are evaluated, each head's result covering its run.
@@ -1680,9 +1681,10 @@ k_score_near(Params p, PointsDev pts, ToolDev t, GridDev g, int64_t n, int32_t m
 // per lane, against the one-bit plane, and the lookups are counted to the
 // deciding hit with a ballot.  The entry-per-lane scan before it walked
 // per-candidate begin offsets and mixed classes; its scalar control flow was
-// as long as its lookups.  What bounds this one is a chunk's chain of two
-// dependent reads (entries, then 64 gathered words: some 500 cycles; address
-// unit 69 %, vector ALU 62 % busy), so:
+// as long as its lookups.  What bounds this one is instruction issue and the
+// address unit's gathers, each some two thirds busy at eight waves a SIMD (two
+// candidates' first words in flight take 2 to 4 % more time), so it reads and
+// counts little, and hides a chunk's chain of two reads (entries, then words):
 //   - the corridor is not read whole: its 4^3 cells name the chunks that can
 //     hit (ToolDev::pent), and only those are read, two in flight;
 //   - the next candidate's chunk and range are requested before the current
@@ -1690,10 +1692,9 @@ k_score_near(Params p, PointsDev pts, ToolDev t, GridDev g, int64_t n, int32_t m
 //   - what depends on the point alone is computed for a batch of points, a
 //     lane each; loops have one exit and no lane-dependent branch, so that
 //     they stay plain scalar control flow.
-// Scoring, before and after (whole call): 1.55 M points x 256 orientations of
-// a tree survey 3340 -> 2500 us; 310 k x 291 790 -> 520 us (the kernel);
-// eight tools of 512 on 0.55 M points 15.9 -> 10.3 ms; four streams in one
-// launch 8.6 -> 5.1 ms.
+// The kernel alone, against the entry-per-lane scan (staged, two corridor
+// chunks in flight) on the same map, 605,000 points of a tree survey: 256
+// orientations 1.20 -> 0.88 ms, 291 1.30 -> 0.90, 1,024 2.53 -> 1.98.
 //
 // An entry's fields leave room for the carries of one add: bits 0-2 of the
 // sum are x in the brick and 3-9 the brick's x, 12-14 and 15-21 y, 22-24 and
@@ -2502,7 +2503,10 @@ static void launch_mask_parts(const Params &p, PointsDev pts, ToolDev t, GridDev
 // call waits for: four waves share 64 points' heads.  Above it they only repeat
 // the points' set-up.  (18,000 points x 64 heads: 40 us with one wave, 16 with
 // four; 59,000 listed points 59 and 32; 310,000 x 97: 131 and 128; 1.15 M
-// 240 and 328.)  A list holds a part of the points that bound it.
+// 240 and 328.)  n bounds the points: a list holds a part of them (one that
+// holds nearly all of 0.3 to 1 M pays up to 40 us for it), and a recorded frame
+// knows only the capacity, so that a small scene in a context of more than
+// kMaskParts points takes one wave.
 constexpr int64_t kMaskParts = 1 << 18;
 
 void launch_mask(const Params &p, PointsDev pts, ToolDev t, GridDev g, int64_t n,
