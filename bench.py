@@ -1198,9 +1198,9 @@ def main():
     roofline = {"kernel": "k_score", "bound": "hbm", "achieved": achieved,
                 "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": achieved / HBM_PEAK_GBS,
                 "traffic": traffic,
-                "limiter": "priced against HBM (algorithmic bytes); the measured limiter is "
-                           "the latency of L2-resident gathers (DRAM traffic is a few percent "
-                           "of the algorithmic bytes)",
+                "limiter": "priced against HBM (algorithmic bytes, nearly all from caches: DRAM "
+                           "traffic is a few percent of them); the measured limiter is "
+                           "instruction issue and the address unit",
                 "dram_over_algorithmic": (traffic / alg_launch) if traffic and alg_launch else None,
                 "algorithmic_bytes_per_launch": alg_launch,
                 "bytes_model": "8 B per canonical lookup not answered by the mask kernel + "

@@ -2503,10 +2503,9 @@ static void launch_mask_parts(const Params &p, PointsDev pts, ToolDev t, GridDev
 // call waits for: four waves share 64 points' heads.  Above it they only repeat
 // the points' set-up.  (18,000 points x 64 heads: 40 us with one wave, 16 with
 // four; 59,000 listed points 59 and 32; 310,000 x 97: 131 and 128; 1.15 M
-// 240 and 328.)  n bounds the points: a list holds a part of them (one that
-// holds nearly all of 0.3 to 1 M pays up to 40 us for it), and a recorded frame
-// knows only the capacity, so that a small scene in a context of more than
-// kMaskParts points takes one wave.
+// 240 and 328.)  n bounds the points: a list holds a part of them (560,000
+// listed: 153 and 156), and a recorded frame knows only the capacity, so that a
+// small scene in a context of more than kMaskParts points takes one wave.
 constexpr int64_t kMaskParts = 1 << 18;
 
 void launch_mask(const Params &p, PointsDev pts, ToolDev t, GridDev g, int64_t n,

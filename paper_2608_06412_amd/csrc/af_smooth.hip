@@ -390,8 +390,9 @@ __device__ inline void unnormalise(const Rot &r, const float tq[3], float dq[4])
 
 // Work distribution: every pair takes the same work, so the groups go round
 // the waves without a counter.  Workgroup i runs on XCD i mod 8, each with its
-// own L2: a wave's place counts the workgroups XCD by XCD, so that (with pairs
-// ordered in space) the waves sharing an L2 read the same part of the map.
+// own L2: a wave's place counts the workgroups XCD by XCD, so that in each round
+// the waves sharing an L2 take neighbouring groups.  (Over the rounds every XCD
+// reads the whole map: of 64 M pairs of ordered points 55 % of the reads hit L2.)
 constexpr int kXcds = 8;
 
 __device__ inline int64_t smooth_wave() {
